@@ -48,10 +48,11 @@ int order_from_env() {
 // sharding) loses more to a part-empty last round of wide tiles. T2V_QTILE=wide or narrow
 // forces one (ablations and tests).
 struct TileRule {
-  int kind = 0;  // 0: dK/dV (one tile shape), 1: forward, 2: dQ
+  int kind = 0;  // 0: dK/dV, 1: forward, 2: dQ
   int wide = 0, narrow = 0;
   bool narrow_always = false;
   double max_loop = 0.0, penalty = 1.0;
+  TileForm forms[2] = {};  // dK/dV: the wide and the narrow form
   int forced = 0;  // 0: chosen by the rule, 1: wide, 2: narrow
   bool same(const TileRule& o) const {
     return kind == o.kind && wide == o.wide && narrow == o.narrow && narrow_always == o.narrow_always &&
@@ -90,10 +91,37 @@ TileRule dq_rule(int head_dim) {
   return r;
 }
 
-TileRule dkdv_rule(int head_dim) {
+// dK/dV at D = 128: 64 keys per wave (256-key tiles) or 32 (128-key tiles, two of which take
+// about one wide tile's time). Item times measured on MI355X with uniform packs of 256 to 65,536
+// tokens at 24 heads; the fixed part is operand loads and output stores with nothing beside them
+// on the CU. Wide is 10-15% faster per unit of work (1,272 against 1,150 TFLOP/s on long clips);
+// narrow wins where wide tiles are half empty (128 keys: 559 against 717 us) or leave CUs idle
+// (8 x 1,024 tokens at 12 heads, 1.5 rounds of wide tiles: 108 against 118 us; 6,912 at 3 heads:
+// 174 against 277 us). Split loops and the persistent grid are in the narrow kernel only,
+// and head_dim 64 has one form. T2V_KVTILE=wide or narrow forces one (ablations and tests).
+TileRule dkdv_rule(int head_dim, int chunk, bool persistent) {
   TileRule r;
-  r.wide = r.narrow = dkdv_tile_rows(head_dim);
+  r.narrow = dkdv_tile_rows(head_dim);
+  r.wide = head_dim == 128 ? dkdv_wide_rows() : r.narrow;
+  r.forms[0] = {r.wide, 1, 12500.0, 52.8};
+  r.forms[1] = {r.narrow, 1, 8000.0, 29.2};
+  const char* s = std::getenv("T2V_KVTILE");
+  if (chunk > 0 || persistent || (s != nullptr && std::strcmp(s, "narrow") == 0))
+    r.forced = 2;
+  else if (s != nullptr && std::strcmp(s, "wide") == 0)
+    r.forced = 1;
   return r;
+}
+
+// The tile rows of a work list: forced, or chosen from the offsets. `items` receives the list
+// when the choice built it.
+int rows_of(const TileRule& r, const int32_t* cu, const int32_t* cu_loop, int nseq, int heads, int order, int ncu,
+            std::vector<Item>* items) {
+  if (r.forced == 1) return r.wide;
+  if (r.forced == 2 || r.wide == r.narrow) return r.narrow;
+  if (r.kind == 0) return r.forms[choose_form(cu, cu_loop, nseq, heads, r.forms, 2, order, ncu, items)].rows;
+  return choose_tile_rows(cu, cu_loop, nseq, heads, r.wide, r.narrow, r.narrow_always, r.max_loop, r.penalty, order,
+                          ncu, items);
 }
 
 // T2V_PERSISTENT=1 launches the forward and dK/dV kernels on a persistent grid (as many
@@ -413,12 +441,7 @@ class PlanCache {
       ncu = 0;
     }
     std::vector<Item> items;
-    const int block = rule.wide == rule.narrow ? rule.wide
-                      : rule.forced == 1       ? rule.wide
-                      : rule.forced == 2       ? rule.narrow
-                                               : choose_tile_rows(cu, cu_loop, nseq, heads, rule.wide, rule.narrow,
-                                                                  rule.narrow_always, rule.max_loop, rule.penalty,
-                                                                  order, ncu, &items);
+    const int block = rows_of(rule, cu, cu_loop, nseq, heads, order, ncu, &items);
     p->rule = rule;
     p->heads = heads;
     p->block = block;
@@ -549,7 +572,7 @@ thread_local bool t_check_armed = false;
 int check_arm() {
   const unsigned int canary = check_canary();
   unsigned int rec[4];
-  for (auto take : {fwd_check_take, dkdv_check_take, dq_check_take}) {
+  for (auto take : {fwd_check_take, dkdv_check_take, dkdv_wide_check_take, dq_check_take}) {
     const hipError_t e = take(rec, canary);
     if (e != hipSuccess) return hip_fail(e, "clearing the DMA row checks");
   }
@@ -561,10 +584,11 @@ int check_arm() {
 int check_collect(hipStream_t s) {
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "waiting for the checked kernels");
-  const char* names[3] = {"forward", "dK/dV", "dQ"};
-  hipError_t (*takes[3])(unsigned int*, unsigned int) = {fwd_check_take, dkdv_check_take, dq_check_take};
+  const char* names[4] = {"forward", "dK/dV", "dK/dV", "dQ"};
+  hipError_t (*takes[4])(unsigned int*, unsigned int) = {fwd_check_take, dkdv_check_take, dkdv_wide_check_take,
+                                                         dq_check_take};
   int status = T2V_OK;
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < 4; ++i) {
     unsigned int rec[4];
     e = takes[i](rec, 0u);
     if (e != hipSuccess) return hip_fail(e, "reading the DMA row checks");
@@ -774,7 +798,8 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
   if (split_enabled())
     chunk = choose_loop_split(cu_k, cu_q, nseq, heads, kv_rows, cu_count(), qb / dkdv_partial_slot_bytes(head_dim))
                 .chunk;
-  if (int st = cache().get(cu_k, cu_q, nseq, heads, dkdv_rule(head_dim), order, chunk, s, &pk)) return st;
+  const TileRule kv_rule = dkdv_rule(head_dim, chunk, persistent_enabled());
+  if (int st = cache().get(cu_k, cu_q, nseq, heads, kv_rule, order, chunk, s, &pk)) return st;
   if (int st = cache().get(cu_q, cu_k, nseq, heads, dq_rule(head_dim), order, 0, s, &pq)) return st;
 #if T2V_CHECKED
   if (int st = check_plan(pk, cu_k, cu_q, nseq, heads, qb / dkdv_partial_slot_bytes(head_dim), "dK/dV")) return st;
@@ -798,6 +823,7 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
   a.total_tokens = Tq;
   a.scale = scale;
   a.persistent = persistent_enabled();
+  a.kv_wide = pk->block != kv_rows;
 #if T2V_CHECKED
   if (int st = check_arm()) return st;
 #endif
@@ -883,7 +909,10 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
   const int ncu = cu_count();
   int chunk = 0;
   if (split_enabled()) chunk = choose_loop_split(cu, cu, nseq, heads, kv_rows, ncu, tb / dkdv_partial_slot_bytes(head_dim)).chunk;
-  std::vector<Item> kv = build_worklist(cu, cu, nseq, heads, kv_rows, order, chunk);
+  const TileRule kv_rule = dkdv_rule(head_dim, chunk, persistent_enabled());
+  std::vector<Item> kv;
+  const int kv_block = rows_of(kv_rule, cu, cu, nseq, heads, order, ncu, &kv);
+  if (kv.empty()) kv = build_worklist(cu, cu, nseq, heads, kv_block, order, chunk);
   const int n_kv = static_cast<int>(kv.size());
   int n_reduce = 0;
   if (chunk > 0) {
@@ -893,13 +922,10 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
   }
   const TileRule qr = dq_rule(head_dim);
   std::vector<Item> ql;
-  const int q_rows = qr.forced == 1   ? qr.wide
-                     : qr.forced == 2 ? qr.narrow
-                                      : choose_tile_rows(cu, cu, nseq, heads, qr.wide, qr.narrow, qr.narrow_always,
-                                                         qr.max_loop, qr.penalty, order, ncu, &ql);
+  const int q_rows = rows_of(qr, cu, cu, nseq, heads, order, ncu, &ql);
   if (ql.empty()) ql = build_worklist(cu, cu, nseq, heads, q_rows, order);
 #if T2V_CHECKED
-  if (int st = check_list(kv, n_kv, n_reduce, cu, cu, nseq, heads, kv_rows, tb / dkdv_partial_slot_bytes(head_dim),
+  if (int st = check_list(kv, n_kv, n_reduce, cu, cu, nseq, heads, kv_block, tb / dkdv_partial_slot_bytes(head_dim),
                           "dK/dV"))
     return st;
   if (int st = check_list(ql, static_cast<int>(ql.size()), 0, cu, cu, nseq, heads, q_rows, 0, "dQ")) return st;
@@ -937,6 +963,7 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
   a.total_tokens = T;
   a.scale = scale;
   a.persistent = persistent_enabled();
+  a.kv_wide = kv_block != kv_rows;
 #if T2V_CHECKED
   if (int st = check_arm()) return st;
 #endif

@@ -377,6 +377,7 @@ void launch_dkdv_as(const AttnArgs& a, const bf16* q, const bf16* k, const bf16*
 }  // namespace
 
 hipError_t launch_bwd_dkdv(const AttnArgs& a, const Item* items, int n_items, hipStream_t stream) {
+  if (a.kv_wide) return launch_bwd_dkdv_wide(a, items, n_items, stream);
   const float c = a.scale * kLog2e;
   const auto* q = static_cast<const bf16*>(a.q);
   const auto* k = static_cast<const bf16*>(a.k);

@@ -320,6 +320,35 @@ T2V_DEV bf16x8 read_rows_opnd(uint32_t base0, uint32_t base1, int row0, int db) 
   return out;
 }
 
+// ------------------------------------------------------- hand-scheduled instruction streams
+//
+// The kernels with one wave per SIMD lay out each step as a fixed sequence of slots, one MFMA
+// plus the LDS reads and vector arithmetic that run under it, because nothing else on the SIMD
+// can hide a stall and the machine schedulers put the arithmetic behind the MFMAs instead of
+// between them. fence() keeps the compiler from moving anything across a slot's end; pin()
+// ties a value to its slot (pure arithmetic would otherwise sink to its use).
+T2V_DEV void fence() { __builtin_amdgcn_sched_barrier(0); }
+T2V_DEV void pin(float& x) { asm volatile("" : "+v"(x)); }
+T2V_DEV void pin(bf16x8& x) { asm volatile("" : "+v"(x)); }
+
+// acc += a b with the accumulator in AGPRs, for the sums that live across the whole loop and
+// that only MFMAs touch: they fill the accumulator half of the register file, so the operands
+// and scores have all 256 VGPRs. The compiler does not look into the assembly for hazards: the
+// s_nop covers the two wait states between a VALU write of a or b and the MFMA that reads it
+// (it issues while the previous MFMA runs), MFMAs on one accumulator interlock in hardware, and
+// acc_settle() must precede the first ordinary read of the accumulators.
+T2V_DEV void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  asm("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+T2V_DEV void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// Lane of the wave, computed afresh so that it need not stay in a register.
+T2V_DEV int lane_again() {
+  unsigned m = ~0u;
+  asm volatile("" : "+s"(m));
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(m, __builtin_amdgcn_mbcnt_lo(m, 0u)));
+}
+
 // ---------------------------------------------------------------- workgroup trace
 //
 // Measurement only. When a launch is traced, each workgroup writes one record of four
@@ -329,10 +358,10 @@ T2V_DEV bf16x8 read_rows_opnd(uint32_t base0, uint32_t base1, int row0, int db) 
 T2V_DEV unsigned long long trace_clock() { return __builtin_amdgcn_s_memrealtime(); }
 
 // Every wave of the workgroup must call this (it holds a barrier); rec is uniform. `index` is the
-// work item's position in the list (the record written).
-T2V_DEV void trace_end(unsigned long long* rec, unsigned long long t0, int slot, int index) {
+// work item's position in the list (the record written), `leader` true in one thread.
+T2V_DEV void trace_end(unsigned long long* rec, unsigned long long t0, int slot, int index, bool leader) {
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (leader) {
     unsigned hw, xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
@@ -343,6 +372,9 @@ T2V_DEV void trace_end(unsigned long long* rec, unsigned long long t0, int slot,
     r[2] = t1;
     r[3] = static_cast<unsigned long long>(slot);
   }
+}
+T2V_DEV void trace_end(unsigned long long* rec, unsigned long long t0, int slot, int index) {
+  trace_end(rec, t0, slot, index, threadIdx.x == 0);
 }
 
 // Eight fp32 to packed bf16 (round to nearest even, v_cvt_pk_bf16_f32).

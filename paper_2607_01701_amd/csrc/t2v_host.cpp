@@ -207,6 +207,63 @@ int choose_tile_rows(const int32_t* cu, const int32_t* cul, int nseq, int heads,
   return take_narrow ? narrow : wide;
 }
 
+namespace {
+// Greedy list-scheduling makespan on `slots` workers, dealt per XCD (item i to XCD i mod 8).
+template <typename Cost>
+double list_makespan(const Item* items, int n, int slots, Cost&& cost) {
+  double span = 0.0;
+  const int groups = (slots % kNumXcd == 0 && slots >= kNumXcd) ? kNumXcd : 1;
+  const int per = slots / groups;
+  for (int x = 0; x < groups && per > 0; ++x) {
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    for (int s = 0; s < per; ++s) free_at.push(0.0);
+    for (int i = x; i < n; i += groups) {
+      const double t0 = free_at.top();
+      free_at.pop();
+      free_at.push(t0 + cost(items[i]));
+    }
+    while (free_at.size() > 1) free_at.pop();
+    span = std::max(span, free_at.top());
+  }
+  return span;
+}
+}  // namespace
+
+int choose_form(const int32_t* cu, const int32_t* cul, int nseq, int heads, const TileForm* forms, int n, int order,
+                int ncu, std::vector<Item>* chosen) {
+  if (n == 1 || ncu < 1) return 0;
+  int best = 0;
+  double best_time = 0.0;
+  std::vector<Item> best_list;
+  for (int f = 0; f < n; ++f) {
+    const TileForm& form = forms[f];
+    double total = 0.0;
+    int64_t items = 0;
+    for (int s = 0; s < nseq; ++s) {
+      const int64_t L = cu[s + 1] - cu[s], LL = cul[s + 1] - cul[s];
+      if (L <= 0 || LL <= 0) continue;
+      const int64_t tiles = (L + form.rows - 1) / form.rows * heads;
+      items += tiles;
+      total += static_cast<double>(tiles) * (form.fixed + form.row * static_cast<double>(LL));
+    }
+    const int64_t slots = static_cast<int64_t>(ncu) * form.per_cu;
+    double time = total / static_cast<double>(slots);
+    std::vector<Item> list;
+    if (items < kManyRounds * slots) {
+      list = build_worklist(cu, cul, nseq, heads, form.rows, order);
+      time = 0.5 * (time + list_makespan(list.data(), static_cast<int>(list.size()), static_cast<int>(slots),
+                                         [&form](const Item& it) { return form.fixed + form.row * it.llen; }));
+    }
+    if (f == 0 || time < best_time) {
+      best = f;
+      best_time = time;
+      best_list = std::move(list);
+    }
+  }
+  if (chosen != nullptr) *chosen = std::move(best_list);
+  return best;
+}
+
 std::vector<Item> build_reduce_list(const int32_t* cu, const int32_t* cul, int nseq, int heads, int block,
                                     int chunk) {
   std::vector<Item> out;
@@ -390,20 +447,7 @@ void plan_makespan(const Item* items, int n, int block, int slots, double* makes
     largest = std::max(largest, cost(items[i]));
   }
   *lower_bound = slots > 0 ? std::max(total / slots, largest) : 0.0;
-  double span = 0.0;
-  const int groups = (slots % kNumXcd == 0 && slots >= kNumXcd) ? kNumXcd : 1;
-  const int per = slots / groups;
-  for (int x = 0; x < groups && per > 0; ++x) {
-    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-    for (int s = 0; s < per; ++s) free_at.push(0.0);
-    for (int i = x; i < n; i += groups) {
-      const double t0 = free_at.top();
-      free_at.pop();
-      free_at.push(t0 + cost(items[i]));
-    }
-    while (free_at.size() > 1) free_at.pop();
-    span = std::max(span, free_at.top());
-  }
+  const double span = list_makespan(items, n, slots, cost);
   *makespan = span;
 }
 

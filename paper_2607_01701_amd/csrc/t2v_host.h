@@ -92,6 +92,25 @@ int choose_tile_rows(const int32_t* cu_own, const int32_t* cu_loop, int nseq, in
                      bool narrow_always, double narrow_max_loop, double narrow_penalty, int order, int slots,
                      std::vector<Item>* chosen = nullptr);
 
+// One form of a kernel: its tile rows, how many of its workgroups a CU holds at once, and the
+// measured time of one item with that many resident, fixed + row * looped-over length (ns).
+struct TileForm {
+  int rows, per_cu;
+  double fixed, row;
+};
+
+// The form with the least predicted time for this pack on `ncu` CUs (the first of equals): the
+// mean of the list-scheduling makespan of the form's work list and the even share of all item
+// times over the slots. The makespan alone is too long by about half of what a part-empty last
+// round leaves idle: under these kernels the card is at its power limit, so the CUs that still
+// run speed up (dK/dV of 75,600 keys at 3 heads, 3.5 rounds of wide tiles: 16.0 ms by makespan,
+// 13.9 by even share, 14.8 measured). Where a form has many rounds (kManyRounds) the even share
+// is taken alone, which needs no list. `chosen` receives the winning list if it was built (else
+// it is left empty).
+constexpr int kManyRounds = 16;
+int choose_form(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int heads, const TileForm* forms, int n,
+                int order, int ncu, std::vector<Item>* chosen);
+
 // One item per split tile of build_worklist(..., chunk): row0, len, tile0, head of the tile,
 // slot = its first partial slot, pieces = the number of consecutive slots to sum.
 std::vector<Item> build_reduce_list(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int heads, int block,

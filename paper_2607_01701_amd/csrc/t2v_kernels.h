@@ -10,9 +10,11 @@
 namespace t2v {
 
 // Rows per work item of each kernel (the tile sizes the scheduler cuts clips into). The
-// forward and dQ kernels come in a wide (8-wave) and a narrow (4-wave) form.
+// forward and dQ kernels come in a wide (8-wave) and a narrow (4-wave) form; the dK/dV kernel
+// in a form of 32 keys per wave (dkdv_tile_rows) and one of 64 (dkdv_wide_rows).
 int fwd_tile_rows(int head_dim, bool narrow);
 int dkdv_tile_rows(int head_dim);
+int dkdv_wide_rows();
 int dq_tile_rows(int head_dim, bool narrow);
 // Bytes of one dK/dV partial slot (fp32 dK and dV of one tile of keys).
 int64_t dkdv_partial_slot_bytes(int head_dim);
@@ -39,6 +41,7 @@ struct AttnArgs {
   // Persistent grid: launch only as many workgroups as the GPU holds at once (a multiple of
   // the 8 XCDs), each taking items w, w + grid, ...; otherwise one workgroup per item.
   bool persistent = false;
+  bool kv_wide = false;  // dK/dV: the 64-keys-per-wave kernel (no loop split, no persistent grid)
 };
 
 // Workgroups of a persistent launch of `kernel` with `threads` threads: the resident
@@ -50,6 +53,7 @@ hipError_t launch_fwd(const AttnArgs& a, void* out, float* lse, const Item* item
                       hipStream_t stream);
 hipError_t launch_bwd_pre(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_bwd_dkdv(const AttnArgs& a, const Item* items, int n_items, hipStream_t stream);
+hipError_t launch_bwd_dkdv_wide(const AttnArgs& a, const Item* items, int n_items, hipStream_t stream);
 hipError_t launch_bwd_dkdv_reduce(const AttnArgs& a, const Item* tiles, int n_tiles, hipStream_t stream);
 hipError_t launch_bwd_dq(const AttnArgs& a, const Item* items, int n_items, hipStream_t stream);
 
@@ -58,6 +62,7 @@ hipError_t launch_bwd_dq(const AttnArgs& a, const Item* items, int n_items, hipS
 // ({violations, first violating workgroup, its row, the segment length}); each call clears
 // the record and sets the canary (rows taken off every bound) for the next launches.
 hipError_t fwd_check_take(unsigned int* rec, unsigned int canary);
+hipError_t dkdv_wide_check_take(unsigned int* rec, unsigned int canary);
 hipError_t dkdv_check_take(unsigned int* rec, unsigned int canary);
 hipError_t dq_check_take(unsigned int* rec, unsigned int canary);
 #endif
