@@ -152,10 +152,18 @@ def host_lib():
 
 
 def _cu_array(cu_seqlens) -> np.ndarray:
+    if type(cu_seqlens) is np.ndarray and cu_seqlens.dtype == np.int32 and cu_seqlens.ndim == 1 \
+            and cu_seqlens.shape[0] >= 1 and cu_seqlens.flags.c_contiguous:
+        return cu_seqlens
     a = np.ascontiguousarray(np.asarray(cu_seqlens, dtype=np.int32))
     if a.ndim != 1 or a.shape[0] < 1:
         raise ValueError("cu_seqlens must be a 1-D array with nseq + 1 entries")
     return a
+
+
+def _offsets_ptr(cu: np.ndarray):
+    """cu's data as an int32 pointer argument (cu outlives the call that takes it)."""
+    return ctypes.byref(ctypes.c_int32.from_address(cu.__array_interface__["data"][0]))
 
 
 def _check(L, status: int):
@@ -272,8 +280,10 @@ def t2v_plan_makespan(items: np.ndarray, block: int, slots: int, L=None):
 
 def _stream_handle(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # torch.cuda.current_stream().cuda_stream without building the Stream object (3 us a call).
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check_tensor(t, name, shape, dtype=None):
@@ -281,7 +291,7 @@ def _check_tensor(t, name, shape, dtype=None):
     (the library sees only pointers, so a wrong size would be read or written past its end)."""
     import torch
     dtype = torch.bfloat16 if dtype is None else dtype
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if t.dtype != dtype:
         raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
@@ -332,12 +342,12 @@ def attn_fwd(q, k, v, cu_seqlens, scale: float, out=None, lse=None, stream=None,
     _check_on_device((("q", q), ("k", k), ("v", v), ("out", out), ("lse", lse)))
     L = lib()
     if cu_seqlens_k is None:
-        st = L.t2v_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), cu.ctypes.data_as(_i32p), cu.shape[0] - 1, H,
+        st = L.t2v_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), _offsets_ptr(cu), cu.shape[0] - 1, H,
                             D, float(scale), out.data_ptr(), lse.data_ptr(), _stream_handle(stream))
     else:
         ck = _cu_array(cu_seqlens_k)
-        st = L.t2v_attn_fwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), cu.ctypes.data_as(_i32p),
-                               ck.ctypes.data_as(_i32p), cu.shape[0] - 1, H, D, float(scale), out.data_ptr(),
+        st = L.t2v_attn_fwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), _offsets_ptr(cu),
+                               _offsets_ptr(ck), cu.shape[0] - 1, H, D, float(scale), out.data_ptr(),
                                lse.data_ptr(), _stream_handle(stream))
     _check(L, st)
     return out, lse
@@ -372,12 +382,12 @@ def attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=None
     L = lib()
     if cu_seqlens_k is None:
         st = L.t2v_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                            cu.ctypes.data_as(_i32p), cu.shape[0] - 1, H, D, float(scale), dout.data_ptr(),
+                            _offsets_ptr(cu), cu.shape[0] - 1, H, D, float(scale), dout.data_ptr(),
                             dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), delta_ws.data_ptr(), _stream_handle(stream))
     else:
         ck = _cu_array(cu_seqlens_k)
         st = L.t2v_attn_bwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                               cu.ctypes.data_as(_i32p), ck.ctypes.data_as(_i32p), cu.shape[0] - 1, H, D, float(scale),
+                               _offsets_ptr(cu), _offsets_ptr(ck), cu.shape[0] - 1, H, D, float(scale),
                                dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), delta_ws.data_ptr(),
                                _stream_handle(stream))
     _check(L, st)

@@ -338,7 +338,7 @@ T2V_DEV void pin(bf16x8& x) { asm volatile("" : "+v"(x)); }
 // (it issues while the previous MFMA runs), MFMAs on one accumulator interlock in hardware, and
 // acc_settle() must precede the first ordinary read of the accumulators.
 T2V_DEV void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  asm("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 T2V_DEV void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
