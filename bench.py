@@ -32,6 +32,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 KERNEL_SOURCES = ("paper_2607_01701_amd/csrc/t2v_fwd.hip", "paper_2607_01701_amd/csrc/t2v_bwd_pre.hip",
                   "paper_2607_01701_amd/csrc/t2v_bwd_dkdv.hip",
                   "paper_2607_01701_amd/csrc/t2v_bwd_dkdv_wide.hip", "paper_2607_01701_amd/csrc/t2v_bwd_dq.hip",
+                  "paper_2607_01701_amd/csrc/t2v_bwd_short.hip",
                   "paper_2607_01701_amd/csrc/t2v_kernel_common.hpp", "paper_2607_01701_amd/csrc/t2v_device.hpp",
                   "paper_2607_01701_amd/csrc/t2v_kernels.h",
                   "paper_2607_01701_amd/csrc/t2v_host.cpp", "paper_2607_01701_amd/csrc/t2v_host.h")

@@ -26,12 +26,15 @@
  *
  * Ownership. The caller owns every buffer. Tensor pointers are device
  * pointers; cu_seqlens is a HOST pointer (the tile scheduler runs on the
- * host). The library keeps only a cache of device work lists keyed by the
- * contents of cu_seqlens (released by t2v_release_cache). It holds up to 64;
+ * host). The library keeps a cache of device work lists keyed by the contents
+ * of cu_seqlens, and the memory of the one-pass backward's partial sums (256 KB
+ * per piece of a segment's queries, a few hundred pieces per call in flight);
+ * t2v_release_cache releases both. It holds up to 64;
  * the call that adds one more releases the least recently used. List memory
  * comes from pooled device and pinned chunks; a released list's memory is
  * reused only after the launches that read it have finished (events recorded
- * on their streams), so no call waits for the device.
+ * on their streams), so no call waits for the device. The partial sums' memory
+ * is handled the same way.
  *
  * Tiles. The forward and dQ kernels own 256-query tiles (8 waves, one workgroup per CU)
  * or 128-query tiles (4 waves, two or three per CU): narrow tiles at head_dim 64, and at
@@ -39,16 +42,22 @@
  * or 8,192 (dQ), where they were measured faster, or when the host's list-scheduling model
  * predicts that the wide tiles would leave CUs idle in a part-empty last round (packs with
  * few tiles per CU, e.g. a long clip at a few heads). The choice is made once per new work
- * list. Both shapes give bitwise-equal results. The dK/dV kernel owns 128-key tiles and loops over the
- * sequence's queries; when the costliest such loop exceeds an even share of the work over
+ * list. Both shapes give bitwise-equal results. The dK/dV kernel owns 256-key or (head_dim 128 only)
+ * 128-key tiles, whichever the host predicts to be faster for the pack (bitwise-equal results),
+ * and loops over the sequence's queries; when the costliest such loop exceeds an even share of the work over
  * the GPU's CUs (few, short key segments against long query segments, as in
  * cross-attention to text), the loops are cut into pieces of at least 2048 queries whose
  * fp32 partial sums are kept in dq's memory and added in piece order before the dQ kernel
  * overwrites dq. Results stay deterministic; they differ from the unsplit order only by
- * rounding.
+ * rounding. Cross-attention at head_dim 128 whose key segments all have at most 256 rows, with
+ * enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs), takes a one-pass
+ * backward instead: one kernel computes Delta, dQ, dK and dV of up to 2048 queries of a
+ * sequence and head, and the fp32 dK / dV of its pieces are added in order (unless the stream is
+ * being captured or their memory cannot be had: then the general path runs).
  *
  * Environment. T2V_ORDER=natural schedules tiles in pack order instead of longest clip
- * first (for ablations); T2V_QTILE=wide or narrow forces the forward / dQ tile shape and
+ * first (for ablations); T2V_QTILE=wide or narrow forces the forward / dQ tile shape,
+ * T2V_KVTILE=wide or narrow the dK/dV one, T2V_SHORT=off disables the one-pass backward and
  * T2V_SPLIT=off disables the dK/dV loop split (ablations and tests); T2V_PERSISTENT=1 runs the
  * forward and dK/dV kernels on a persistent grid (as many workgroups as the GPU holds at once,
  * each striding over the work list; bitwise-equal results, measured ~1% slower, so off by

@@ -28,7 +28,7 @@ CHECKED_LIB = os.path.join(PKG, "libt2vattn_checked.so")
 CHECKED_FLAGS = ["-DT2V_CHECKED=1"]
 
 HIP_SOURCES = ["t2v_fwd.hip", "t2v_bwd_pre.hip", "t2v_bwd_dkdv.hip", "t2v_bwd_dkdv_wide.hip",
-               "t2v_bwd_dq.hip", "t2v_api.hip", "t2v_probe.hip"]
+               "t2v_bwd_dq.hip", "t2v_bwd_short.hip", "t2v_api.hip", "t2v_probe.hip"]
 HOST_SOURCES = ["t2v_host.cpp", "t2v_plan.cpp"]
 
 ARCH = os.environ.get("T2V_OFFLOAD_ARCH", "gfx950")

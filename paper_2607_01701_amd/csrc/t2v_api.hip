@@ -48,7 +48,7 @@ int order_from_env() {
 // sharding) loses more to a part-empty last round of wide tiles. T2V_QTILE=wide or narrow
 // forces one (ablations and tests).
 struct TileRule {
-  int kind = 0;  // 0: dK/dV, 1: forward, 2: dQ
+  int kind = 0;  // 0: dK/dV, 1: forward, 2: dQ, 3: one-pass backward of short key segments
   int wide = 0, narrow = 0;
   bool narrow_always = false;
   double max_loop = 0.0, penalty = 1.0;
@@ -131,6 +131,36 @@ int rows_of(const TileRule& r, const int32_t* cu, const int32_t* cu_loop, int ns
 bool persistent_enabled() {
   const char* s = std::getenv("T2V_PERSISTENT");
   return s != nullptr && std::strcmp(s, "1") == 0;
+}
+
+// One-pass backward (t2v_bwd_short.hip) for cross-attention to short key segments: every segment
+// fits a workgroup (256 keys), and the queries fill the CUs 2.5 times with pieces of at least
+// kShortMinPiece rows. A piece costs about 28 us besides its queries (K and V in, fp32 dK and dV
+// out and in again for the sum), so short pieces lose what the one pass saves. Measured on 116,904
+// queries x 12 heads against 32-256 keys: general path 818-839 us; one pass with pieces of 512
+// rows 680, 1,024 583-604, 1,536 543-550, 2,048 533-538, 4,096 573 (too few to balance).
+// Returns the piece length, or 0 for the general path. T2V_SHORT=off selects that (ablations and
+// tests). Self-attention takes the general path, which t2v_attn_bwd_noalloc shares.
+constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048;
+int short_piece(const int32_t* cu_q, const int32_t* cu_k, int nseq, int heads, int head_dim, int ncu) {
+  const char* s = std::getenv("T2V_SHORT");
+  if (head_dim != 128 || ncu < 1 || (s != nullptr && std::strcmp(s, "off") == 0)) return 0;
+  if (cu_q == cu_k || std::memcmp(cu_q, cu_k, sizeof(int32_t) * (nseq + 1)) == 0) return 0;
+  for (int i = 0; i < nseq; ++i)
+    if (cu_k[i + 1] - cu_k[i] > short_keys()) return 0;
+  const int64_t share = 2 * static_cast<int64_t>(heads) * cu_q[nseq] / (5 * ncu);
+  if (share < kShortMinPiece) return 0;
+  return static_cast<int>(std::min<int64_t>(share / 64 * 64, kShortMaxPiece));
+}
+
+// A step of a one-pass item takes about 1.6 times as long with 129 to 256 keys as with fewer.
+double short_weight(int32_t keys) { return keys > short_keys() / 2 ? 1.6 : 1.0; }
+
+TileRule short_rule() {
+  TileRule r;
+  r.kind = 3;
+  r.wide = r.narrow = short_keys();
+  return r;
 }
 
 // T2V_SPLIT=off disables the dK/dV loop split (for ablations).
@@ -359,6 +389,7 @@ struct Plan {
   int heads = 0, block = 0, order = 0, device = 0, chunk = 0;
   Item* d_items = nullptr;  // n_items work items, then n_reduce split tiles (loop split)
   int n_items = 0, n_reduce = 0;
+  int64_t n_slots = 0;  // partial slots the items write
   ListPool::Block mem;             // d_items' block in the device pool
   hipEvent_t ready = nullptr;      // upload finished (from the device pool's event pool)
   std::vector<std::pair<hipStream_t, hipEvent_t>> uses;  // last launch reading d_items, per stream
@@ -448,11 +479,13 @@ class PlanCache {
     p->order = order;
     p->device = device;
     p->chunk = chunk;
-    if (items.empty() || chunk > 0) items = build_worklist(cu, cu_loop, nseq, heads, block, order, chunk);
+    if (items.empty() || chunk > 0)
+      items = build_worklist(cu, cu_loop, nseq, heads, block, order, chunk, rule.kind == 3 ? short_weight : nullptr);
     p->n_items = static_cast<int>(items.size());
     if (chunk > 0) {
       const std::vector<Item> red = build_reduce_list(cu, cu_loop, nseq, heads, block, chunk);
       p->n_reduce = static_cast<int>(red.size());
+      for (const Item& it : red) p->n_slots += it.pieces;
       items.insert(items.end(), red.begin(), red.end());
     }
     const size_t bytes = items.size() * sizeof(Item);
@@ -572,7 +605,7 @@ thread_local bool t_check_armed = false;
 int check_arm() {
   const unsigned int canary = check_canary();
   unsigned int rec[4];
-  for (auto take : {fwd_check_take, dkdv_check_take, dkdv_wide_check_take, dq_check_take}) {
+  for (auto take : {fwd_check_take, dkdv_check_take, dkdv_wide_check_take, dq_check_take, short_check_take}) {
     const hipError_t e = take(rec, canary);
     if (e != hipSuccess) return hip_fail(e, "clearing the DMA row checks");
   }
@@ -584,11 +617,11 @@ int check_arm() {
 int check_collect(hipStream_t s) {
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "waiting for the checked kernels");
-  const char* names[4] = {"forward", "dK/dV", "dK/dV", "dQ"};
-  hipError_t (*takes[4])(unsigned int*, unsigned int) = {fwd_check_take, dkdv_check_take, dkdv_wide_check_take,
-                                                         dq_check_take};
+  const char* names[5] = {"forward", "dK/dV", "dK/dV", "dQ", "one-pass backward"};
+  hipError_t (*takes[5])(unsigned int*, unsigned int) = {fwd_check_take, dkdv_check_take, dkdv_wide_check_take,
+                                                         dq_check_take, short_check_take};
   int status = T2V_OK;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 5; ++i) {
     unsigned int rec[4];
     e = takes[i](rec, 0u);
     if (e != hipSuccess) return hip_fail(e, "reading the DMA row checks");
@@ -768,6 +801,57 @@ int attn_fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu
   return used;
 }
 
+// The one-pass backward: *taken = false (and nothing launched) when its partial slots cannot be
+// had, i.e. the allocation failed or the stream is being captured (a graph would keep them).
+// The slots come from the device's list pool and return to it once the launches have completed.
+int attn_bwd_short(const AttnArgs& args, const int32_t* cu_q, const int32_t* cu_k, int nseq, int piece, int order,
+                   hipStream_t s, bool* taken) {
+  *taken = false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return T2V_OK;
+  }
+  PlanRef plan;
+  if (int st = cache().get(cu_k, cu_q, nseq, args.heads, short_rule(), order, piece, s, &plan)) return st;
+#if T2V_CHECKED
+  if (int st = check_plan(plan, cu_k, cu_q, nseq, args.heads, plan->n_slots, "one-pass backward")) return st;
+#endif
+  DevicePools& dp = pools(plan->device);
+  ListPool::Block slots;
+  if (plan->n_slots > 0) {
+    std::lock_guard<std::mutex> lock(dp.mu);
+    if (dp.dev.alloc(static_cast<uint64_t>(plan->n_slots * short_partial_slot_bytes()), &slots) != T2V_OK) return T2V_OK;
+  }
+  *taken = true;
+  AttnArgs a = args;
+  a.partial = static_cast<float*>(slots.ptr);
+  int st = T2V_OK;
+#if T2V_CHECKED
+  st = check_arm();
+#endif
+  hipError_t e = hipSuccess;
+  if (st == T2V_OK && plan->n_items > 0) {
+    a.trace = tracer().reserve(plan->n_items);
+    e = timer().run(kSlotDkdv, s, [&] {
+      return launch_bwd_short(a, plan->d_items, plan->n_items, plan->d_items + plan->n_items, plan->n_reduce, s);
+    });
+    st = note_use(plan, s);
+  }
+  std::lock_guard<std::mutex> lock(dp.mu);
+  hipEvent_t ev = nullptr;
+  hipError_t r = dp.dev.take_event(&ev);
+  if (r == hipSuccess) r = hipEventRecord(ev, s);
+  if (r != hipSuccess) {
+    if (ev != nullptr) (void)hipEventDestroy(ev);
+    (void)hipStreamSynchronize(s);
+    dp.dev.release_after(slots, {});
+    return hip_fail(r, "hipEventRecord after launch");
+  }
+  dp.dev.release_after(slots, {ev});
+  return e != hipSuccess ? hip_fail(e, "one-pass backward launch") : st;
+}
+
 int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, const float* lse, const int32_t* cu_q,
                   const int32_t* cu_k, int nseq, int heads, int head_dim, float scale, const void* dout, void* dq,
                   void* dk, void* dv, float* delta_ws, void* stream) {
@@ -788,6 +872,26 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
     return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int order = order_from_env();
+  AttnArgs a{};
+  a.q = q;
+  a.k = k;
+  a.v = v;
+  a.out = out;
+  a.lse = lse;
+  a.dout = dout;
+  a.dq = dq;
+  a.dk = dk;
+  a.dv = dv;
+  a.delta = delta_ws;
+  a.heads = heads;
+  a.head_dim = head_dim;
+  a.total_tokens = Tq;
+  a.scale = scale;
+  if (const int piece = short_piece(cu_q, cu_k, nseq, heads, head_dim, cu_count())) {
+    bool taken = false;
+    const int st = attn_bwd_short(a, cu_q, cu_k, nseq, piece, order, s, &taken);
+    if (st != T2V_OK || taken) return st;
+  }
   PlanRef pk, pq;
   // dK/dV tiles own keys and loop over queries; dQ tiles own queries and loop over keys.
   // Loops too long for the available parallelism (short keys, long queries) are split into
@@ -805,23 +909,8 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
   if (int st = check_plan(pk, cu_k, cu_q, nseq, heads, qb / dkdv_partial_slot_bytes(head_dim), "dK/dV")) return st;
   if (int st = check_plan(pq, cu_q, cu_k, nseq, heads, 0, "dQ")) return st;
 #endif
-  AttnArgs a{};
   a.q_rows = pq->block;
   a.partial = static_cast<float*>(dq);
-  a.q = q;
-  a.k = k;
-  a.v = v;
-  a.out = out;
-  a.lse = lse;
-  a.dout = dout;
-  a.dq = dq;
-  a.dk = dk;
-  a.dv = dv;
-  a.delta = delta_ws;
-  a.heads = heads;
-  a.head_dim = head_dim;
-  a.total_tokens = Tq;
-  a.scale = scale;
   a.persistent = persistent_enabled();
   a.kv_wide = pk->block != kv_rows;
 #if T2V_CHECKED

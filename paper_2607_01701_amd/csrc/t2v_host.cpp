@@ -310,7 +310,7 @@ std::string check_work_items(const Item* items, int n, const int32_t* cu_own, co
 }
 
 std::vector<Item> build_worklist(const int32_t* cu, const int32_t* cu_loop, int nseq, int heads, int block,
-                                 int order, int chunk) {
+                                 int order, int chunk, double (*weight)(int32_t)) {
   std::vector<Group> groups = make_groups(cu, cu_loop, nseq, heads, block, chunk);
   std::vector<Item> items;
   size_t n = 0;
@@ -323,7 +323,8 @@ std::vector<Item> build_worklist(const int32_t* cu, const int32_t* cu_loop, int 
   // Longest tiles first (a tile costs its rows times the looped-over length; for
   // self-attention this is the longest clip first); ties keep pack order, so one
   // (sequence, head)'s tiles stay adjacent.
-  std::stable_sort(groups.begin(), groups.end(), [](const Group& a, const Group& b) { return a.llen > b.llen; });
+  auto cost = [&](const Group& g) { return (weight != nullptr ? weight(g.len) : block) * static_cast<double>(g.llen); };
+  std::stable_sort(groups.begin(), groups.end(), [&](const Group& a, const Group& b) { return cost(a) > cost(b); });
   // Workgroup b runs on XCD b % 8, and each XCD starts its share in increasing b, so every
   // XCD takes the same number of items. Deal whole (clip, head) groups to the least-loaded
   // XCD that has room for them and stays within an even share of the total cost, so the
@@ -335,10 +336,10 @@ std::vector<Item> build_worklist(const int32_t* cu, const int32_t* cu_loop, int 
   std::vector<std::vector<Item>> q(kNumXcd);
   std::vector<double> load(kNumXcd, 0.0);
   double total = 0.0;
-  for (const auto& g : groups) total += static_cast<double>(g.tiles) * block * g.llen;
+  for (const auto& g : groups) total += static_cast<double>(g.tiles) * cost(g);
   const double share = total / kNumXcd * (1.0 + 1e-9);
   for (const auto& g : groups) {
-    const double item_cost = static_cast<double>(block) * g.llen;
+    const double item_cost = cost(g);
     int t = 0;
     while (t < g.tiles) {
       const size_t want = static_cast<size_t>(g.tiles - t);
@@ -384,7 +385,7 @@ std::vector<Item> build_worklist(const int32_t* cu, const int32_t* cu_loop, int 
         for (int x = 0; x < kNumXcd; ++x)
           if (cap[x] > qi[x].size() && (best < 0 || li[x] < li[best])) best = x;
         qi[best].push_back(it);
-        li[best] += static_cast<double>(block) * it.llen;
+        li[best] += cost(g);
       }
     }
     if (imbalance(li) < grouped) q.swap(qi);

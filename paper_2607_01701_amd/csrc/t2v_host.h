@@ -59,8 +59,10 @@ int validate_shape_qk(const int32_t* cu_q, const int32_t* cu_k, int nseq, int he
 // longer than chunk rows into pieces (loop_pieces), one item per tile and piece; the
 // partial slot of (sequence s, head h, tile t, piece j) is base(s, h) + t * pieces + j, with
 // base counted over the split (sequence, head) pairs in pack order.
+// `weight` (if given) is the cost of one looped-over row for a segment of that many owned rows
+// (default: the tile rows), which the order and the dealing to XCDs go by.
 std::vector<Item> build_worklist(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int heads, int block,
-                                 int order, int chunk = 0);
+                                 int order, int chunk = 0, double (*weight)(int32_t len) = nullptr);
 
 // Pieces of a loop of LL rows cut at chunk rows: *n pieces of *step rows (a multiple of
 // 64), the last taking the rest. *n = 1 (step = LL) when chunk <= 0 or LL <= chunk.

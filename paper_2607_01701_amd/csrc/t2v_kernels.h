@@ -57,11 +57,19 @@ hipError_t launch_bwd_dkdv_wide(const AttnArgs& a, const Item* items, int n_item
 hipError_t launch_bwd_dkdv_reduce(const AttnArgs& a, const Item* tiles, int n_tiles, hipStream_t stream);
 hipError_t launch_bwd_dq(const AttnArgs& a, const Item* items, int n_items, hipStream_t stream);
 
+// The one-pass backward for key segments of at most short_keys() rows (t2v_bwd_short.hip):
+// `items` own whole key segments and loop over pieces of the queries; `segs` is the reduce list.
+int short_keys();
+int64_t short_partial_slot_bytes();
+hipError_t launch_bwd_short(const AttnArgs& a, const Item* items, int n_items, const Item* segs, int n_segs,
+                            hipStream_t stream);
+
 #if T2V_CHECKED
 // Checked builds only: the DMA row record of the forward, dK/dV and dQ kernel sources
 // ({violations, first violating workgroup, its row, the segment length}); each call clears
 // the record and sets the canary (rows taken off every bound) for the next launches.
 hipError_t fwd_check_take(unsigned int* rec, unsigned int canary);
+hipError_t short_check_take(unsigned int* rec, unsigned int canary);
 hipError_t dkdv_wide_check_take(unsigned int* rec, unsigned int canary);
 hipError_t dkdv_check_take(unsigned int* rec, unsigned int canary);
 hipError_t dq_check_take(unsigned int* rec, unsigned int canary);

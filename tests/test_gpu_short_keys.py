@@ -1,0 +1,96 @@
+"""The one-pass backward for cross-attention to short key segments (at most 256 keys each, many
+queries): gradients against the float64 oracle and the general path at the edges of its tiles
+(key counts around 32, 64, 128 and 256; query counts around its 32-query steps, its three LDS
+stages and its pieces), bitwise reproducible also while other streams run it, and delta_ws
+holding -Delta and lse * log2(e) as after the general path."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_01701_amd.workload import bf16_bits_to_f32, make_pack_qk
+
+from gpu_util import assert_within, dev_inputs, log, rel_err
+
+pytestmark = pytest.mark.gpu
+
+LQ = [3000, 1, 31, 33, 96, 97, 2049, 1500, 64, 65]
+LK = [1, 32, 33, 128, 129, 256, 255, 64, 65, 100]
+HEADS = 64
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _backward(d, pack, out, lse):
+    import torch
+    from paper_2607_01701_amd import attn_bwd
+    ws = torch.full((2, pack.heads, pack.total_tokens), float("nan"), dtype=torch.float32, device="cuda")
+    g = attn_bwd(d["q"], d["k"], d["v"], out, lse, d["dout"], pack.cu_seqlens, pack.scale, delta_ws=ws,
+                 cu_seqlens_k=pack.cu_seqlens_k)
+    return dict(zip(("dq", "dk", "dv"), g), ws=ws)
+
+
+def test_short_key_backward(monkeypatch, capfd):
+    import torch
+    from paper_2607_01701_amd import attn_fwd, t2v_release_cache
+    pack = make_pack_qk(LQ, LK, HEADS, 128, seed=91)
+    log(f"case one-pass backward lq={LQ} lk={LK} H={HEADS}")
+    d = dev_inputs(pack)
+    out, lse = attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, cu_seqlens_k=pack.cu_seqlens_k)
+    t2v_release_cache()
+    monkeypatch.setenv("T2V_LOG", "1")
+    a = _backward(d, pack, out, lse)
+    torch.cuda.synchronize()
+    err = capfd.readouterr().err
+    assert "256-row tiles" in err and "loops split at" in err, err
+    monkeypatch.delenv("T2V_LOG")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    again = []
+    for s in streams:  # concurrent calls have partial slots of their own
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            again.append(_backward(d, pack, out, lse))
+    torch.cuda.synchronize()
+    for b in again:
+        for n in a:
+            assert torch.equal(a[n], b[n]), f"{n} is not reproducible"
+    monkeypatch.setenv("T2V_SHORT", "off")
+    g = _backward(d, pack, out, lse)
+    torch.cuda.synchronize()
+    # fp32 sums of the same products in another order (128 terms of order 1)
+    assert torch.allclose(a["ws"], g["ws"], rtol=1e-5, atol=1e-4)
+    heads = [0, HEADS - 1]
+    f = {n: bf16_bits_to_f32(np.ascontiguousarray(getattr(pack, n)[:, heads])) for n in ("q", "k", "v", "dout")}
+    ref = oracle.attention(f["q"], f["k"], f["v"], f["dout"], pack.cu_seqlens, pack.scale,
+                           cu_seqlens_k=pack.cu_seqlens_k)
+    errs = {"out": 0.0, "lse": 0.0}
+    for n in ("dq", "dk", "dv"):
+        got = a[n][:, heads].double().cpu().numpy()
+        errs[n] = rel_err(got, ref[n])
+        # The general path rounds P, dS and the result at the same places; each is within 2^-8 of the exact result.
+        assert rel_err(a[n].double().cpu().numpy(), g[n].double().cpu().numpy()) <= 2e-2, n
+    log(f"  errors {errs}")
+    assert_within(errs)
+
+
+def test_few_queries_and_equal_offsets_keep_the_general_path(monkeypatch, capfd):
+    """Too few queries to fill the CUs, a segment of 257 keys, or offsets equal to the queries'
+    (self-attention): bitwise what T2V_SHORT=off gives."""
+    import torch
+    from paper_2607_01701_amd import attn_fwd
+    for lq, lk, H in (([3000, 500], [100, 256], 2), ([20000, 500], [100, 257], 20), ([200] * 40, [200] * 40, 64)):
+        pack = make_pack_qk(lq, lk, H, 128, seed=92)
+        log(f"case general path lq={lq[:2]} lk={lk[:2]} H={H}")
+        d = dev_inputs(pack)
+        out, lse = attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, cu_seqlens_k=pack.cu_seqlens_k)
+        monkeypatch.delenv("T2V_SHORT", raising=False)
+        a = _backward(d, pack, out, lse)
+        monkeypatch.setenv("T2V_SHORT", "off")
+        b = _backward(d, pack, out, lse)
+        torch.cuda.synchronize()
+        for n in a:
+            assert torch.equal(a[n], b[n]), n
