@@ -190,19 +190,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void attn_bwd_dq_kernel(
   #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         const int qi = q_wave0 + qb * 32 + l32;
-        if (qi < Lq) {
-          bf16* row = dq + base + qi * rs;
   #pragma unroll
-          for (int db = 0; db < DB; ++db) {
-  #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              bf16x4 w;
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) w[e] = static_cast<bf16>(dqa[qb][db][i * 4 + e] * scale);
-              *reinterpret_cast<bf16x4*>(row + db * 32 + i * 8 + G * 4) = w;
-            }
-          }
-        }
+        for (int db = 0; db < DB; ++db) store_rows(dq + base + qi * rs + db * 32, dqa[qb][db], scale, G, qi < Lq);
       }
     }
     if (trace != nullptr) trace_end(trace, trace_t0, 3, w);

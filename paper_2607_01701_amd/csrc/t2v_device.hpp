@@ -394,6 +394,31 @@ T2V_DEV float half_sum(float x) {
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
+// Stores a transposed accumulator (32 rows x 32 columns: lane = row, register r = column
+// 8 (r/4) + 4 G + r % 4) times `mul` as bf16. `row` is this lane's row at column 0, written when
+// `valid`. The two lanes of a row swap four-column groups first, so that each stores 16 bytes:
+// half the store instructions, in 32-byte pieces of a row instead of 16. Where stores weigh most, in
+// cross-attention to 31-226 keys, the forward takes 68 us instead of 83, and 60 instead of 63 for
+// images of 1,024 tokens; whole rows through LDS measured the same.
+T2V_DEV void store_rows(bf16* row, const f32x16& acc, float mul, int G, bool valid) {
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    u32x2 x[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = static_cast<bf16>(acc[(i + j) * 4 + e] * mul);
+      x[j] = __builtin_bit_cast(u32x2, w);
+    }
+    const auto lo = __builtin_amdgcn_permlane32_swap(x[0][0], x[1][0], false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(x[0][1], x[1][1], false, false);
+    // G = 0: columns 8i .. 8i+7; G = 1: columns 8i+8 .. 8i+15.
+    const u32x4 y = {lo[0], hi[0], lo[1], hi[1]};
+    if (valid) *reinterpret_cast<u32x4*>(row + i * 8 + G * 8) = y;
+  }
+}
+
 // NaN-propagating maximum / minimum (v_maximum3_f32 / v_minimum3_f32 on gfx950). Unlike
 // fmaxf / fminf they need no canonicalising copies of operands that come straight from an
 // MFMA, and a NaN score carries through to a NaN output instead of being dropped.

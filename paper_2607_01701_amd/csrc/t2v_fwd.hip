@@ -239,18 +239,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void attn_fwd_kernel(
         const int qi = q_wave0 + qb * 32 + l32;
         const float lt = half_sum(l_run[qb]);
         const float inv = 1.0f / lt;
+  #pragma unroll
+        for (int db = 0; db < DB; ++db) store_rows(out + base + qi * rs + db * 32, o[qb][db], inv, G, qi < Lq);
         if (qi < Lq) {
-          bf16* orow = out + base + qi * rs;
-  #pragma unroll
-          for (int db = 0; db < DB; ++db) {
-  #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              bf16x4 w;
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) w[e] = static_cast<bf16>(o[qb][db][i * 4 + e] * inv);
-              *reinterpret_cast<bf16x4*>(orow + db * 32 + i * 8 + G * 4) = w;
-            }
-          }
           if (G == 0) lse[static_cast<int64_t>(it.head) * T + it.row0 + qi] = (m_run[qb] + __builtin_amdgcn_logf(lt)) * kLn2;
         }
       }
