@@ -27,14 +27,14 @@
  * Ownership. The caller owns every buffer. Tensor pointers are device
  * pointers; cu_seqlens is a HOST pointer (the tile scheduler runs on the
  * host). The library keeps a cache of device work lists keyed by the contents
- * of cu_seqlens, and the memory of the one-pass backward's partial sums (256 KB
- * per piece of a segment's queries, a few hundred pieces per call in flight);
- * t2v_release_cache releases both. It holds up to 64;
+ * of cu_seqlens. It holds up to 64;
  * the call that adds one more releases the least recently used. List memory
  * comes from pooled device and pinned chunks; a released list's memory is
  * reused only after the launches that read it have finished (events recorded
- * on their streams), so no call waits for the device. The partial sums' memory
- * is handled the same way.
+ * on their streams), so no call waits for the device. It also keeps buffers for
+ * the partial sums of the one-pass backward (256 KB per piece of a segment's
+ * queries, a few hundred pieces; calls in a row on one stream share one buffer,
+ * at most 1 GiB in all). t2v_release_cache releases both.
  *
  * Tiles. The forward and dQ kernels own 256-query tiles (8 waves, one workgroup per CU)
  * or 128-query tiles (4 waves, two or three per CU): narrow tiles at head_dim 64, and at

@@ -139,9 +139,12 @@ bool persistent_enabled() {
 // out and in again for the sum), so short pieces lose what the one pass saves. Measured on 116,904
 // queries x 12 heads against 32-256 keys: general path 818-839 us; one pass with pieces of 512
 // rows 680, 1,024 583-604, 1,536 543-550, 2,048 533-538, 4,096 573 (too few to balance).
+// Above kShortMaxPieces pieces (eight per CU, which balance as well as more) the pieces grow instead:
+// cutting a segment into equal pieces at most doubles their number, so a call's partial sums stay
+// under 1 GiB.
 // Returns the piece length, or 0 for the general path. T2V_SHORT=off selects that (ablations and
 // tests). Self-attention takes the general path, which t2v_attn_bwd_noalloc shares.
-constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048;
+constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048, kShortMaxPieces = 2048;
 int short_piece(const int32_t* cu_q, const int32_t* cu_k, int nseq, int heads, int head_dim, int ncu) {
   const char* s = std::getenv("T2V_SHORT");
   if (head_dim != 128 || ncu < 1 || (s != nullptr && std::strcmp(s, "off") == 0)) return 0;
@@ -150,7 +153,9 @@ int short_piece(const int32_t* cu_q, const int32_t* cu_k, int nseq, int heads, i
     if (cu_k[i + 1] - cu_k[i] > short_keys()) return 0;
   const int64_t share = 2 * static_cast<int64_t>(heads) * cu_q[nseq] / (5 * ncu);
   if (share < kShortMinPiece) return 0;
-  return static_cast<int>(std::min<int64_t>(share / 64 * 64, kShortMaxPiece));
+  const int64_t least = (static_cast<int64_t>(heads) * cu_q[nseq] / kShortMaxPieces + 63) / 64 * 64;
+  const int64_t piece = std::max(std::min<int64_t>(share / 64 * 64, kShortMaxPiece), least);
+  return static_cast<int>(std::min<int64_t>(piece, 1 << 30));
 }
 
 // A step of a one-pass item takes about 1.6 times as long with 129 to 256 keys as with fewer.
@@ -341,10 +346,101 @@ class ListPool {
   std::vector<hipEvent_t> events_;
 };
 
-// Both pools of one device, and the lock that guards them.
+// Memory of the one-pass backward's partial sums, per device. A buffer serves one call at a time;
+// the next one to take it waits, on its stream, for the event recorded behind the last. Calls in a
+// row on one stream share one buffer (that wait is then no wait), calls on several streams have
+// one each while the total stays under kMax, and share after that. Nothing here waits on the host.
+class SlotPool {
+ public:
+  struct Buffer {
+    void* ptr;
+    uint64_t bytes;
+    hipEvent_t last;     // behind the last call that used it
+    hipStream_t stream;  // of that call: compared only
+    bool taken;
+  };
+  // Caller holds mu(). A buffer of at least `bytes`, to be used on `s` and given back with
+  // release(); nullptr if none can be had.
+  Buffer* acquire(uint64_t bytes, hipStream_t s) {
+    if (fail_alloc_for_test()) return nullptr;
+    const uint64_t want = (bytes + kRound - 1) / kRound * kRound;
+    Buffer* b = find(want, [&](const Buffer& x) { return x.stream == s; });
+    if (b == nullptr) b = find(want, [](const Buffer& x) { return idle(x); });
+    if (b == nullptr) b = add(want, s);
+    if (b == nullptr) b = find(want, [](const Buffer&) { return true; });
+    if (b == nullptr) return nullptr;
+    if (hipStreamWaitEvent(s, b->last, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    b->taken = true;
+    return b;
+  }
+  // Caller holds mu(). The launches on `s` that use the buffer are enqueued.
+  hipError_t release(Buffer* b, hipStream_t s) {
+    const hipError_t e = hipEventRecord(b->last, s);
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    b->stream = s;
+    b->taken = false;
+    return e;
+  }
+  // Caller holds the lock and has synchronised the device: frees what no launch since then uses.
+  void trim_after_sync() {
+    drop([](const Buffer& b) { return idle(b); });
+  }
+
+ private:
+  static constexpr uint64_t kRound = 32ull << 20, kMax = 1ull << 30;
+  static bool idle(const Buffer& b) {
+    if (hipEventQuery(b.last) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+  }
+  template <typename F>
+  Buffer* find(uint64_t bytes, F&& ok) {
+    for (auto& b : all_)
+      if (!b.taken && b.bytes >= bytes && ok(b)) return &b;
+    return nullptr;
+  }
+  template <typename F>
+  void drop(F&& ok) {
+    for (auto it = all_.begin(); it != all_.end();) {
+      if (it->taken || !ok(*it)) {
+        ++it;
+        continue;
+      }
+      (void)hipFree(it->ptr);
+      (void)hipEventDestroy(it->last);
+      total_ -= it->bytes;
+      it = all_.erase(it);
+    }
+  }
+  Buffer* add(uint64_t bytes, hipStream_t s) {
+    drop([&](const Buffer& b) { return b.bytes < bytes && idle(b); });  // outgrown
+    if (total_ + bytes > kMax) return nullptr;
+    Buffer b{nullptr, bytes, nullptr, s, false};
+    if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (hipEventCreateWithFlags(&b.last, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipFree(b.ptr);
+      return nullptr;
+    }
+    all_.push_back(b);
+    total_ += bytes;
+    return &all_.back();
+  }
+  std::list<Buffer> all_;
+  uint64_t total_ = 0;
+};
+
+// The pools of one device, and the lock that guards them.
 struct DevicePools {
   std::mutex mu;
   ListPool dev{false}, pin{true};
+  SlotPool slots;
 };
 
 std::mutex& pools_mu() {
@@ -376,6 +472,7 @@ void trim_pools_after_sync() {
     std::lock_guard<std::mutex> lock(p->mu);
     p->dev.trim_after_sync();
     p->pin.trim_after_sync();
+    p->slots.trim_after_sync();
   }
 }
 
@@ -803,7 +900,6 @@ int attn_fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu
 
 // The one-pass backward: *taken = false (and nothing launched) when its partial slots cannot be
 // had, i.e. the allocation failed or the stream is being captured (a graph would keep them).
-// The slots come from the device's list pool and return to it once the launches have completed.
 int attn_bwd_short(const AttnArgs& args, const int32_t* cu_q, const int32_t* cu_k, int nseq, int piece, int order,
                    hipStream_t s, bool* taken) {
   *taken = false;
@@ -818,14 +914,15 @@ int attn_bwd_short(const AttnArgs& args, const int32_t* cu_q, const int32_t* cu_
   if (int st = check_plan(plan, cu_k, cu_q, nseq, args.heads, plan->n_slots, "one-pass backward")) return st;
 #endif
   DevicePools& dp = pools(plan->device);
-  ListPool::Block slots;
+  SlotPool::Buffer* slots = nullptr;
   if (plan->n_slots > 0) {
     std::lock_guard<std::mutex> lock(dp.mu);
-    if (dp.dev.alloc(static_cast<uint64_t>(plan->n_slots * short_partial_slot_bytes()), &slots) != T2V_OK) return T2V_OK;
+    slots = dp.slots.acquire(static_cast<uint64_t>(plan->n_slots * short_partial_slot_bytes()), s);
+    if (slots == nullptr) return T2V_OK;
   }
   *taken = true;
   AttnArgs a = args;
-  a.partial = static_cast<float*>(slots.ptr);
+  a.partial = slots != nullptr ? static_cast<float*>(slots->ptr) : nullptr;
   int st = T2V_OK;
 #if T2V_CHECKED
   st = check_arm();
@@ -838,18 +935,14 @@ int attn_bwd_short(const AttnArgs& args, const int32_t* cu_q, const int32_t* cu_
     });
     st = note_use(plan, s);
   }
-  std::lock_guard<std::mutex> lock(dp.mu);
-  hipEvent_t ev = nullptr;
-  hipError_t r = dp.dev.take_event(&ev);
-  if (r == hipSuccess) r = hipEventRecord(ev, s);
-  if (r != hipSuccess) {
-    if (ev != nullptr) (void)hipEventDestroy(ev);
-    (void)hipStreamSynchronize(s);
-    dp.dev.release_after(slots, {});
-    return hip_fail(r, "hipEventRecord after launch");
+  hipError_t r = hipSuccess;
+  if (slots != nullptr) {
+    std::lock_guard<std::mutex> lock(dp.mu);
+    r = dp.slots.release(slots, s);
   }
-  dp.dev.release_after(slots, {ev});
-  return e != hipSuccess ? hip_fail(e, "one-pass backward launch") : st;
+  if (e != hipSuccess) return hip_fail(e, "one-pass backward launch");
+  if (st == T2V_OK && r != hipSuccess) return hip_fail(r, "hipEventRecord after launch");
+  return st;
 }
 
 int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, const float* lse, const int32_t* cu_q,
