@@ -226,6 +226,7 @@ def copy_calibration():
 
 
 SLOT_OF_KERNEL = {"attn_fwd_kernel": "fwd", "attn_bwd_pre_kernel": "bwd_pre", "attn_bwd_dkdv_kernel": "bwd_dkdv",
+                  "attn_bwd_dkdv_wide_kernel": "bwd_dkdv",
                   "attn_bwd_dq_kernel": "bwd_dq"}
 
 

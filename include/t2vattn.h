@@ -51,8 +51,8 @@
  * overwrites dq. Results stay deterministic; they differ from the unsplit order only by
  * rounding. Cross-attention at head_dim 128 whose key segments all have at most 256 rows, with
  * enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs), takes a one-pass
- * backward instead: one kernel computes Delta, dQ, dK and dV of up to 2048 queries of a
- * sequence and head, and the fp32 dK / dV of its pieces are added in order (unless the stream is
+ * backward instead: one kernel computes Delta, dQ, dK and dV of a piece of a sequence's queries
+ * (up to 2048, more on the largest packs) and one head, and the fp32 dK / dV of its pieces are added in order (unless the stream is
  * being captured or their memory cannot be had: then the general path runs).
  *
  * Environment. T2V_ORDER=natural schedules tiles in pack order instead of longest clip
