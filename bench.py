@@ -494,8 +494,11 @@ def write_summaries(bench_json, sweep_jsonl=None):
             cc, kk = r["config"], r["kernels"]
             name = cc["workload"].split(":")[0]
             vals[(name, cc["scheduler_order"])] = r["value"]
-            ks = (f"{kk['fwd']['tflops']:.0f} / {kk['bwd_dkdv']['tflops']:.0f} / {kk['bwd_dq']['tflops']:.0f}, "
-                  f"{kk['bwd_pre']['gbs']:.0f}")
+            # A kernel that the workload did not launch (the one-pass backward has one for all) shows "-".
+            shown = [(kk.get(n) or {}).get(u) for n, u in (("fwd", "tflops"), ("bwd_dkdv", "tflops"),
+                                                           ("bwd_dq", "tflops"), ("bwd_pre", "gbs"))]
+            f, dkdv, dq, pre = ("-" if x is None else f"{x:.0f}" for x in shown)
+            ks = f"{f} / {dkdv} / {dq}, {pre}"
             out.append(f"{name:9s} {cc['scheduler_order']:14s} {r['steps']:5d} {r['ms_per_step']:10.3f} "
                        f"{r['value']:10.1f} {100 * r['frac_of_peak']:6.1f}% {r['fwd_tflops']:9.1f} "
                        f"{r['bwd_tflops']:9.1f}  {ks}")
