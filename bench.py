@@ -1024,6 +1024,14 @@ def run_workload(workload, seed, steps, warmup, order=None, device_values=False)
     stream = torch.cuda.current_stream()
     sh = stream.cuda_stream
     cup = cu.ctypes.data_as(_lib._i32p)
+    ws = torch.empty(0, dtype=torch.uint8, device="cuda")
+    if cross:  # the workspace that the backward asks for (nothing is launched without it)
+        st, _, most = _lib.t2v_attn_bwd_qk_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                                              cu, cuk, nseq, H, D, pack.scale, g.data_ptr(), dq.data_ptr(),
+                                              dk.data_ptr(), dv.data_ptr(), delta.data_ptr(), None, 0, sh)
+        if st not in (_lib.T2V_OK, _lib.T2V_ERR_WORKSPACE):
+            raise _lib.T2VError(st, _lib.t2v_last_error())
+        ws = torch.empty(most, dtype=torch.uint8, device="cuda")
 
     def step(mid=None):
         if cross:
@@ -1037,9 +1045,9 @@ def run_workload(workload, seed, steps, warmup, order=None, device_values=False)
         if mid is not None:
             mid.record(stream)
         if cross:
-            st = L.t2v_attn_bwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), cup, cukp,
-                                   nseq, H, D, pack.scale, g.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-                                   delta.data_ptr(), sh)
+            st = L.t2v_attn_bwd_qk_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), cup,
+                                      cukp, nseq, H, D, pack.scale, g.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                                      dv.data_ptr(), delta.data_ptr(), ws.data_ptr(), ws.numel(), None, sh)
         else:
             st = L.t2v_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), cup, nseq,
                                 H, D, pack.scale, g.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
@@ -1144,7 +1152,7 @@ def run_workload(workload, seed, steps, warmup, order=None, device_values=False)
         res["config"]["total_tokens_k"] = pack.total_tokens_k
     if order is not None:
         res["config"]["scheduler_order"] = order
-    del q, k, v, g, out, dq, dk, dv, lse, delta
+    del q, k, v, g, out, dq, dk, dv, lse, delta, ws
     torch.cuda.empty_cache()
     return res, pack
 

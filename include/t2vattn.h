@@ -31,10 +31,7 @@
  * the call that adds one more releases the least recently used. List memory
  * comes from pooled device and pinned chunks; a released list's memory is
  * reused only after the launches that read it have finished (events recorded
- * on their streams), so no call waits for the device. It also keeps buffers for
- * the partial sums of the one-pass backward (256 KB per piece of a segment's
- * queries, a few hundred pieces; calls in a row on one stream share one buffer,
- * at most 1 GiB in all). t2v_release_cache releases both.
+ * on their streams), so no call waits for the device. t2v_release_cache releases them.
  *
  * Tiles. The forward and dQ kernels own 256-query tiles (8 waves, one workgroup per CU)
  * or 128-query tiles (4 waves, two or three per CU): narrow tiles at head_dim 64, and at
@@ -49,11 +46,12 @@
  * cross-attention to text), the loops are cut into pieces of at least 2048 queries whose
  * fp32 partial sums are kept in dq's memory and added in piece order before the dQ kernel
  * overwrites dq. Results stay deterministic; they differ from the unsplit order only by
- * rounding. Cross-attention at head_dim 128 whose key segments all have at most 256 rows, with
- * enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs), takes a one-pass
- * backward instead: one kernel computes Delta, dQ, dK and dV of a piece of a sequence's queries
- * (up to 2048, more on the largest packs) and one head, and the fp32 dK / dV of its pieces are added in order (unless the stream is
- * being captured or their memory cannot be had: then the general path runs).
+ * rounding. t2v_attn_bwd_qk_ws, given device memory for the partial sums, takes a one-pass
+ * backward instead for cross-attention at head_dim 128 whose key segments all have at most 256
+ * rows, with enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs): one kernel
+ * computes Delta, dQ, dK and dV of a piece of a sequence's queries (up to 2048, more on the
+ * largest packs) and one head, and the fp32 dK / dV of its pieces are added in order. Which path a
+ * call takes follows from the entry point, its offsets and sizes, and the environment below alone.
  *
  * Environment. T2V_ORDER=natural schedules tiles in pack order instead of longest clip
  * first (for ablations); T2V_QTILE=wide or narrow forces the forward / dQ tile shape,
@@ -104,8 +102,9 @@ typedef enum {
   T2V_ERR_UNSUPPORTED = 2, /* head_dim other than 64 or 128 */
   T2V_ERR_HIP = 3,         /* a HIP runtime call or kernel launch failed */
   T2V_ERR_OOM = 4,         /* the work-list cache could not allocate */
-  T2V_ERR_BOUNDS = 5       /* checked library only: a work item, or a row a kernel copies,
+  T2V_ERR_BOUNDS = 5,      /* checked library only: a work item, or a row a kernel copies,
                               lies outside its clip (see "Checked library" below) */
+  T2V_ERR_WORKSPACE = 6    /* t2v_attn_bwd_qk_ws only: the workspace is too small */
 } t2v_status;
 
 /* Tile orders for the scheduler (see t2v_build_worklist). */
@@ -188,6 +187,25 @@ int t2v_attn_bwd_qk(const void* q, const void* k, const void* v,
                     int heads, int head_dim, float scale,
                     const void* dout, void* dq, void* dk, void* dv, float* delta_ws,
                     void* stream);
+
+/* t2v_attn_bwd_qk with a workspace, which lets it take the one-pass backward (see Tiles above;
+ * measured 1.5x faster on captions of 32 to 256 tokens). t2v_attn_bwd_qk itself takes no memory and always the general path.
+ *   ws        device memory, 16-byte aligned, scratch during the call (as delta_ws: the next call
+ *             on the same stream may use it too); must not overlap any other argument
+ *   ws_bytes  its size; 0 (with ws NULL) if there is none
+ *   need      host uint64_t[2] or NULL; receives the least and the most bytes this call can use,
+ *             both 0 when it needs none
+ * With fewer than need[0] bytes nothing is launched and T2V_ERR_WORKSPACE is returned, so a
+ * first call with ws NULL asks for the size. Between the two, heads are processed in batches, with
+ * bitwise the same results. need[0] is need[1] / heads; need[1] is 256 KB per piece of a sequence's
+ * queries and head, at most 1 GiB. Everything else is as in t2v_attn_bwd_qk; where the one-pass
+ * backward runs, dk and dv differ from t2v_attn_bwd_qk's by rounding (another order of the sums). */
+int t2v_attn_bwd_qk_ws(const void* q, const void* k, const void* v,
+                       const void* out, const float* lse,
+                       const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k, int nseq,
+                       int heads, int head_dim, float scale,
+                       const void* dout, void* dq, void* dk, void* dv, float* delta_ws,
+                       void* ws, uint64_t ws_bytes, uint64_t* need, void* stream);
 
 /* Thread-local message describing the last non-OK status of this thread. */
 const char* t2v_last_error(void);

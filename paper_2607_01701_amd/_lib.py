@@ -25,8 +25,9 @@ T2V_ERR_UNSUPPORTED = 2
 T2V_ERR_HIP = 3
 T2V_ERR_OOM = 4
 T2V_ERR_BOUNDS = 5
+T2V_ERR_WORKSPACE = 6
 STATUS_NAMES = {0: "T2V_OK", 1: "T2V_ERR_INVALID_ARG", 2: "T2V_ERR_UNSUPPORTED", 3: "T2V_ERR_HIP",
-                4: "T2V_ERR_OOM", 5: "T2V_ERR_BOUNDS"}
+                4: "T2V_ERR_OOM", 5: "T2V_ERR_BOUNDS", 6: "T2V_ERR_WORKSPACE"}
 
 ORDER_NATURAL = 0
 ORDER_LONGEST_FIRST = 1
@@ -35,13 +36,14 @@ ORDER_LONGEST_FIRST = 1
 EXPORTS = ("t2v_attn_fwd", "t2v_attn_bwd", "t2v_attn_fwd_qk", "t2v_attn_bwd_qk", "t2v_last_error",
            "t2v_release_cache", "t2v_build_worklist", "t2v_plan_makespan", "t2v_timing_enable", "t2v_kernel_times",
            "t2v_version", "t2v_list_schedule", "t2v_plan_cascades", "t2v_probe_mfma_peak", "t2v_trace_set",
-           "t2v_trace_count", "t2v_attn_bwd_noalloc")
+           "t2v_trace_count", "t2v_attn_bwd_noalloc", "t2v_attn_bwd_qk_ws")
 KERNEL_SLOTS = ("fwd", "bwd_pre", "bwd_dkdv", "bwd_dq")
 HOST_EXPORTS = ("t2v_last_error", "t2v_build_worklist", "t2v_plan_makespan", "t2v_version", "t2v_list_schedule",
                 "t2v_plan_cascades")
 
 _vp = ctypes.c_void_p
 _i32p = ctypes.POINTER(ctypes.c_int32)
+_u64p = ctypes.POINTER(ctypes.c_uint64)
 _f32p = ctypes.c_void_p  # device float* passed as an address
 
 
@@ -85,6 +87,8 @@ def _declare(lib, full: bool):
         lib.t2v_attn_bwd_qk.restype = ctypes.c_int
         lib.t2v_attn_bwd_qk.argtypes = [_vp, _vp, _vp, _vp, _f32p, _i32p, _i32p, ctypes.c_int, ctypes.c_int,
                                         ctypes.c_int, ctypes.c_float, _vp, _vp, _vp, _vp, _f32p, _vp]
+        lib.t2v_attn_bwd_qk_ws.restype = ctypes.c_int
+        lib.t2v_attn_bwd_qk_ws.argtypes = [*lib.t2v_attn_bwd_qk.argtypes[:-1], _vp, ctypes.c_uint64, _u64p, _vp]
         lib.t2v_release_cache.restype = None
         lib.t2v_release_cache.argtypes = []
         lib.t2v_timing_enable.restype = ctypes.c_int
@@ -209,6 +213,16 @@ def t2v_attn_bwd_qk(q, k, v, out, lse, cu_seqlens_q, cu_seqlens_k, nseq, heads, 
                                  head_dim, scale, dout, dq, dk, dv, delta_ws, stream)
 
 
+def t2v_attn_bwd_qk_ws(q, k, v, out, lse, cu_seqlens_q, cu_seqlens_k, nseq, heads, head_dim, scale, dout, dq, dk, dv,
+                       delta_ws, ws, ws_bytes, stream):
+    """Direct call of t2v_attn_bwd_qk_ws with integer addresses; returns (status, least, most bytes of ws)."""
+    cq, ck = _cu_array(cu_seqlens_q), _cu_array(cu_seqlens_k)
+    need = (ctypes.c_uint64 * 2)()
+    st = lib().t2v_attn_bwd_qk_ws(q, k, v, out, lse, cq.ctypes.data_as(_i32p), ck.ctypes.data_as(_i32p), nseq, heads,
+                                  head_dim, scale, dout, dq, dk, dv, delta_ws, ws, ws_bytes, need, stream)
+    return st, need[0], need[1]
+
+
 def t2v_last_error(L=None) -> str:
     return (L or lib()).t2v_last_error().decode()
 
@@ -284,6 +298,20 @@ def _stream_handle(stream):
         return stream.cuda_stream
     # torch.cuda.current_stream().cuda_stream without building the Stream object (3 us a call).
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _scratch(most: int, least: int, device, stream):
+    """Device memory for one call on `stream`: `most` bytes, or as many as can be had by halving down
+    to `least`. It belongs to that stream, so it can be dropped as soon as the call has returned."""
+    import torch
+    with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
+        while True:
+            try:
+                return torch.empty(most, dtype=torch.uint8, device=device)
+            except torch.cuda.OutOfMemoryError:
+                if most == least:
+                    raise
+                most = max(least, most // 2)
 
 
 def _check_tensor(t, name, shape, dtype=None):
@@ -386,9 +414,15 @@ def attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=None
                             dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), delta_ws.data_ptr(), _stream_handle(stream))
     else:
         ck = _cu_array(cu_seqlens_k)
-        st = L.t2v_attn_bwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                               _offsets_ptr(cu), _offsets_ptr(ck), cu.shape[0] - 1, H, D, float(scale),
-                               dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), delta_ws.data_ptr(),
-                               _stream_handle(stream))
+        need = (ctypes.c_uint64 * 2)()
+        ws, st = None, T2V_ERR_WORKSPACE
+        while st == T2V_ERR_WORKSPACE:  # twice at most: the first call says what workspace it needs, if any
+            if need[0]:
+                ws = _scratch(need[1], need[0], q.device, stream)
+            st = L.t2v_attn_bwd_qk_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                                      _offsets_ptr(cu), _offsets_ptr(ck), cu.shape[0] - 1, H, D, float(scale),
+                                      dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
+                                      delta_ws.data_ptr(), None if ws is None else ws.data_ptr(),
+                                      0 if ws is None else ws.numel(), need, _stream_handle(stream))
     _check(L, st)
     return dq, dk, dv

@@ -141,7 +141,7 @@ bool persistent_enabled() {
 // rows 680, 1,024 583-604, 1,536 543-550, 2,048 533-538, 4,096 573 (too few to balance).
 // Above kShortMaxPieces pieces (eight per CU, which balance as well as more) the pieces grow instead:
 // cutting a segment into equal pieces at most doubles their number, so a call's partial sums stay
-// under 1 GiB.
+// under 1 GiB (the caller's workspace).
 // Returns the piece length, or 0 for the general path. T2V_SHORT=off selects that (ablations and
 // tests). Self-attention takes the general path, which t2v_attn_bwd_noalloc shares.
 constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048, kShortMaxPieces = 2048;
@@ -346,101 +346,10 @@ class ListPool {
   std::vector<hipEvent_t> events_;
 };
 
-// Memory of the one-pass backward's partial sums, per device. A buffer serves one call at a time;
-// the next one to take it waits, on its stream, for the event recorded behind the last. Calls in a
-// row on one stream share one buffer (that wait is then no wait), calls on several streams have
-// one each while the total stays under kMax, and share after that. Nothing here waits on the host.
-class SlotPool {
- public:
-  struct Buffer {
-    void* ptr;
-    uint64_t bytes;
-    hipEvent_t last;     // behind the last call that used it
-    hipStream_t stream;  // of that call: compared only
-    bool taken;
-  };
-  // Caller holds mu(). A buffer of at least `bytes`, to be used on `s` and given back with
-  // release(); nullptr if none can be had.
-  Buffer* acquire(uint64_t bytes, hipStream_t s) {
-    if (fail_alloc_for_test()) return nullptr;
-    const uint64_t want = (bytes + kRound - 1) / kRound * kRound;
-    Buffer* b = find(want, [&](const Buffer& x) { return x.stream == s; });
-    if (b == nullptr) b = find(want, [](const Buffer& x) { return idle(x); });
-    if (b == nullptr) b = add(want, s);
-    if (b == nullptr) b = find(want, [](const Buffer&) { return true; });
-    if (b == nullptr) return nullptr;
-    if (hipStreamWaitEvent(s, b->last, 0) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    b->taken = true;
-    return b;
-  }
-  // Caller holds mu(). The launches on `s` that use the buffer are enqueued.
-  hipError_t release(Buffer* b, hipStream_t s) {
-    const hipError_t e = hipEventRecord(b->last, s);
-    if (e != hipSuccess) (void)hipStreamSynchronize(s);
-    b->stream = s;
-    b->taken = false;
-    return e;
-  }
-  // Caller holds the lock and has synchronised the device: frees what no launch since then uses.
-  void trim_after_sync() {
-    drop([](const Buffer& b) { return idle(b); });
-  }
-
- private:
-  static constexpr uint64_t kRound = 32ull << 20, kMax = 1ull << 30;
-  static bool idle(const Buffer& b) {
-    if (hipEventQuery(b.last) == hipSuccess) return true;
-    (void)hipGetLastError();
-    return false;
-  }
-  template <typename F>
-  Buffer* find(uint64_t bytes, F&& ok) {
-    for (auto& b : all_)
-      if (!b.taken && b.bytes >= bytes && ok(b)) return &b;
-    return nullptr;
-  }
-  template <typename F>
-  void drop(F&& ok) {
-    for (auto it = all_.begin(); it != all_.end();) {
-      if (it->taken || !ok(*it)) {
-        ++it;
-        continue;
-      }
-      (void)hipFree(it->ptr);
-      (void)hipEventDestroy(it->last);
-      total_ -= it->bytes;
-      it = all_.erase(it);
-    }
-  }
-  Buffer* add(uint64_t bytes, hipStream_t s) {
-    drop([&](const Buffer& b) { return b.bytes < bytes && idle(b); });  // outgrown
-    if (total_ + bytes > kMax) return nullptr;
-    Buffer b{nullptr, bytes, nullptr, s, false};
-    if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    if (hipEventCreateWithFlags(&b.last, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      (void)hipFree(b.ptr);
-      return nullptr;
-    }
-    all_.push_back(b);
-    total_ += bytes;
-    return &all_.back();
-  }
-  std::list<Buffer> all_;
-  uint64_t total_ = 0;
-};
-
 // The pools of one device, and the lock that guards them.
 struct DevicePools {
   std::mutex mu;
   ListPool dev{false}, pin{true};
-  SlotPool slots;
 };
 
 std::mutex& pools_mu() {
@@ -472,7 +381,6 @@ void trim_pools_after_sync() {
     std::lock_guard<std::mutex> lock(p->mu);
     p->dev.trim_after_sync();
     p->pin.trim_after_sync();
-    p->slots.trim_after_sync();
   }
 }
 
@@ -486,7 +394,6 @@ struct Plan {
   int heads = 0, block = 0, order = 0, device = 0, chunk = 0;
   Item* d_items = nullptr;  // n_items work items, then n_reduce split tiles (loop split)
   int n_items = 0, n_reduce = 0;
-  int64_t n_slots = 0;  // partial slots the items write
   ListPool::Block mem;             // d_items' block in the device pool
   hipEvent_t ready = nullptr;      // upload finished (from the device pool's event pool)
   std::vector<std::pair<hipStream_t, hipEvent_t>> uses;  // last launch reading d_items, per stream
@@ -582,7 +489,6 @@ class PlanCache {
     if (chunk > 0) {
       const std::vector<Item> red = build_reduce_list(cu, cu_loop, nseq, heads, block, chunk);
       p->n_reduce = static_cast<int>(red.size());
-      for (const Item& it : red) p->n_slots += it.pieces;
       items.insert(items.end(), red.begin(), red.end());
     }
     const size_t bytes = items.size() * sizeof(Item);
@@ -898,56 +804,77 @@ int attn_fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu
   return used;
 }
 
-// The one-pass backward: *taken = false (and nothing launched) when its partial slots cannot be
-// had, i.e. the allocation failed or the stream is being captured (a graph would keep them).
+// Device memory that a caller of t2v_attn_bwd_qk_ws offers for the partial sums of the one-pass
+// backward, and what the call could use: {least, most} bytes.
+struct Workspace {
+  void* ptr;
+  uint64_t bytes;
+  uint64_t need[2];
+};
+
+// The one-pass backward, over as many heads at a time as the workspace has partial slots for.
+// The pieces follow from the whole call's offsets and heads, so the results do not depend on how
+// many batches of heads there are.
 int attn_bwd_short(const AttnArgs& args, const int32_t* cu_q, const int32_t* cu_k, int nseq, int piece, int order,
-                   hipStream_t s, bool* taken) {
-  *taken = false;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return T2V_OK;
+                   Workspace* ws, hipStream_t s) {
+  const uint64_t slot_bytes = static_cast<uint64_t>(short_partial_slot_bytes());
+  const uint64_t per_head =
+      static_cast<uint64_t>(split_slots(cu_k, cu_q, nseq, short_keys(), piece)) * slot_bytes;
+  ws->need[0] = per_head;
+  ws->need[1] = per_head * args.heads;
+  int batch = args.heads;
+  if (per_head > 0) {
+    if (ws->bytes < per_head)
+      return set_error(T2V_ERR_WORKSPACE, "the one-pass backward needs " + std::to_string(per_head) +
+                                              " bytes of workspace or more, got " + std::to_string(ws->bytes));
+    const int most = static_cast<int>(std::min<uint64_t>(ws->bytes / per_head, batch));
+    const int n = (batch + most - 1) / most;
+    batch = (batch + n - 1) / n;
   }
-  PlanRef plan;
-  if (int st = cache().get(cu_k, cu_q, nseq, args.heads, short_rule(), order, piece, s, &plan)) return st;
+  for (int h0 = 0; h0 < args.heads; h0 += batch) {
+    const int heads = std::min(batch, args.heads - h0);
+    PlanRef plan;
+    if (int st = cache().get(cu_k, cu_q, nseq, heads, short_rule(), order, piece, s, &plan)) return st;
 #if T2V_CHECKED
-  if (int st = check_plan(plan, cu_k, cu_q, nseq, args.heads, plan->n_slots, "one-pass backward")) return st;
+    if (int st = check_plan(plan, cu_k, cu_q, nseq, heads, static_cast<int64_t>(ws->bytes / slot_bytes),
+                            "one-pass backward"))
+      return st;
+    if (h0 == 0)
+      if (int st = check_arm()) return st;
 #endif
-  DevicePools& dp = pools(plan->device);
-  SlotPool::Buffer* slots = nullptr;
-  if (plan->n_slots > 0) {
-    std::lock_guard<std::mutex> lock(dp.mu);
-    slots = dp.slots.acquire(static_cast<uint64_t>(plan->n_slots * short_partial_slot_bytes()), s);
-    if (slots == nullptr) return T2V_OK;
-  }
-  *taken = true;
-  AttnArgs a = args;
-  a.partial = slots != nullptr ? static_cast<float*>(slots->ptr) : nullptr;
-  int st = T2V_OK;
-#if T2V_CHECKED
-  st = check_arm();
-#endif
-  hipError_t e = hipSuccess;
-  if (st == T2V_OK && plan->n_items > 0) {
+    if (plan->n_items == 0) continue;
+    AttnArgs a = args;
+    // Head h0 of a [T, H, D] bf16 tensor.
+    const int64_t off = static_cast<int64_t>(h0) * args.head_dim * 2;
+    auto in = [off](const void* p) { return static_cast<const char*>(p) + off; };
+    auto grad = [off](void* p) { return static_cast<char*>(p) + off; };
+    a.q = in(args.q);
+    a.k = in(args.k);
+    a.v = in(args.v);
+    a.out = in(args.out);
+    a.dout = in(args.dout);
+    a.dq = grad(args.dq);
+    a.dk = grad(args.dk);
+    a.dv = grad(args.dv);
+    a.lse += h0 * args.total_tokens;
+    a.delta += h0 * args.total_tokens;
+    a.partial = static_cast<float*>(ws->ptr);
     a.trace = tracer().reserve(plan->n_items);
-    e = timer().run(kSlotDkdv, s, [&] {
+    const hipError_t e = timer().run(kSlotDkdv, s, [&] {
       return launch_bwd_short(a, plan->d_items, plan->n_items, plan->d_items + plan->n_items, plan->n_reduce, s);
     });
-    st = note_use(plan, s);
+    const int used = note_use(plan, s);
+    if (e != hipSuccess) return hip_fail(e, "one-pass backward launch");
+    if (used != T2V_OK) return used;
   }
-  hipError_t r = hipSuccess;
-  if (slots != nullptr) {
-    std::lock_guard<std::mutex> lock(dp.mu);
-    r = dp.slots.release(slots, s);
-  }
-  if (e != hipSuccess) return hip_fail(e, "one-pass backward launch");
-  if (st == T2V_OK && r != hipSuccess) return hip_fail(r, "hipEventRecord after launch");
-  return st;
+  return T2V_OK;
 }
 
+// ws: the caller's workspace, with which the one-pass backward may be taken; nullptr: the general
+// path, which needs none.
 int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, const float* lse, const int32_t* cu_q,
                   const int32_t* cu_k, int nseq, int heads, int head_dim, float scale, const void* dout, void* dq,
-                  void* dk, void* dv, float* delta_ws, void* stream) {
+                  void* dk, void* dv, float* delta_ws, void* stream, Workspace* ws = nullptr) {
   if (int st = check_offsets_on_host(cu_q, cu_k)) return st;
   int64_t Tq = 0, Tk = 0;
   if (cu_q == cu_k) {
@@ -959,9 +886,10 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
   if (Tq == 0) return T2V_OK;
   const int64_t qb = tensor_bytes(Tq, heads, head_dim), kb = tensor_bytes(Tk, heads, head_dim);
   const int64_t lb = Tq * heads * 4;
+  std::vector<Range> outputs = {{dq, qb, "dq"}, {dk, kb, "dk"}, {dv, kb, "dv"}, {delta_ws, 2 * lb, "delta_ws"}};
+  if (ws != nullptr && ws->bytes > 0) outputs.push_back({ws->ptr, static_cast<int64_t>(ws->bytes), "ws"});
   if (int st = validate_pointers(
-          {{q, qb, "q"}, {k, kb, "k"}, {v, kb, "v"}, {out, qb, "out"}, {lse, lb, "lse"}, {dout, qb, "dout"}},
-          {{dq, qb, "dq"}, {dk, kb, "dk"}, {dv, kb, "dv"}, {delta_ws, 2 * lb, "delta_ws"}}))
+          {{q, qb, "q"}, {k, kb, "k"}, {v, kb, "v"}, {out, qb, "out"}, {lse, lb, "lse"}, {dout, qb, "dout"}}, outputs))
     return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int order = order_from_env();
@@ -980,11 +908,8 @@ int attn_bwd_impl(const void* q, const void* k, const void* v, const void* out, 
   a.head_dim = head_dim;
   a.total_tokens = Tq;
   a.scale = scale;
-  if (const int piece = short_piece(cu_q, cu_k, nseq, heads, head_dim, cu_count())) {
-    bool taken = false;
-    const int st = attn_bwd_short(a, cu_q, cu_k, nseq, piece, order, s, &taken);
-    if (st != T2V_OK || taken) return st;
-  }
+  if (const int piece = ws != nullptr ? short_piece(cu_q, cu_k, nseq, heads, head_dim, cu_count()) : 0)
+    return attn_bwd_short(a, cu_q, cu_k, nseq, piece, order, ws, s);
   PlanRef pk, pq;
   // dK/dV tiles own keys and loop over queries; dQ tiles own queries and loop over keys.
   // Loops too long for the available parallelism (short keys, long queries) are split into
@@ -1270,6 +1195,26 @@ int t2v_attn_bwd_qk(const void* q, const void* k, const void* v, const void* out
       return t2v::attn_bwd_impl(q, k, v, out, lse, cu_seqlens_q, cu_seqlens_k, nseq, heads, head_dim, scale, dout,
                                 dq, dk, dv, delta_ws, stream);
     });
+  });
+}
+
+int t2v_attn_bwd_qk_ws(const void* q, const void* k, const void* v, const void* out, const float* lse,
+                       const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k, int nseq, int heads, int head_dim,
+                       float scale, const void* dout, void* dq, void* dk, void* dv, float* delta_ws, void* ws,
+                       uint64_t ws_bytes, uint64_t* need, void* stream) {
+  return t2v::guarded([&] {
+    if (cu_seqlens_q == nullptr || cu_seqlens_k == nullptr)
+      return t2v::set_error(T2V_ERR_INVALID_ARG, "cu_seqlens_q or cu_seqlens_k is NULL");
+    t2v::Workspace w{ws, ws_bytes, {0, 0}};
+    const int st = t2v::checked_call(stream, [&] {
+      return t2v::attn_bwd_impl(q, k, v, out, lse, cu_seqlens_q, cu_seqlens_k, nseq, heads, head_dim, scale, dout,
+                                dq, dk, dv, delta_ws, stream, &w);
+    });
+    if (need != nullptr) {
+      need[0] = w.need[0];
+      need[1] = w.need[1];
+    }
+    return st;
   });
 }
 

@@ -155,6 +155,18 @@ void loop_pieces(int LL, int chunk, int* n, int* step) {
   *step = s;
 }
 
+int64_t split_slots(const int32_t* cu, const int32_t* cul, int nseq, int block, int chunk) {
+  int64_t slots = 0;
+  for (int s = 0; s < nseq; ++s) {
+    const int32_t L = cu[s + 1] - cu[s], LL = cul[s + 1] - cul[s];
+    if (L <= 0 || LL <= 0) continue;
+    int n = 1, step = LL;
+    loop_pieces(LL, chunk, &n, &step);
+    if (n > 1) slots += static_cast<int64_t>((L + block - 1) / block) * n;
+  }
+  return slots;
+}
+
 LoopSplit choose_loop_split(const int32_t* cu, const int32_t* cul, int nseq, int heads, int block, int parallel,
                             int64_t max_slots) {
   double total = 0.0, largest = 0.0;
@@ -170,14 +182,7 @@ LoopSplit choose_loop_split(const int32_t* cu, const int32_t* cul, int nseq, int
   const double share = std::ceil(total / (2.0 * parallel * block));
   int64_t chunk = std::max<int64_t>(kMinChunk, (static_cast<int64_t>(share) + 63) / 64 * 64);
   for (; chunk < longest; chunk *= 2) {  // widen the pieces until their partial slots fit
-    int64_t slots = 0;
-    for (int s = 0; s < nseq; ++s) {
-      const int32_t L = cu[s + 1] - cu[s], LL = cul[s + 1] - cul[s];
-      if (L <= 0 || LL <= 0) continue;
-      int n = 1, step = LL;
-      loop_pieces(LL, static_cast<int>(chunk), &n, &step);
-      if (n > 1) slots += static_cast<int64_t>(heads) * ((L + block - 1) / block) * n;
-    }
+    const int64_t slots = heads * split_slots(cu, cul, nseq, block, static_cast<int>(chunk));
     if (slots == 0) return {};
     if (slots <= max_slots && slots <= INT32_MAX) return {static_cast<int>(chunk), slots};
   }

@@ -113,6 +113,9 @@ constexpr int kManyRounds = 16;
 int choose_form(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int heads, const TileForm* forms, int n,
                 int order, int ncu, std::vector<Item>* chosen);
 
+// Partial slots that build_worklist(..., chunk) numbers per head.
+int64_t split_slots(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int block, int chunk);
+
 // One item per split tile of build_worklist(..., chunk): row0, len, tile0, head of the tile,
 // slot = its first partial slot, pieces = the number of consecutive slots to sum.
 std::vector<Item> build_reduce_list(const int32_t* cu_own, const int32_t* cu_loop, int nseq, int heads, int block,

@@ -402,3 +402,37 @@ def test_noalloc_refuses_a_pack_beyond_its_scratch_before_any_device_call():
                                 H, D, 0.125, p[5], p[6], p[7], p[8], None)
     msg = _lib.t2v_last_error(L)
     assert st == INV and "bytes of scratch" in msg and "67108864" in msg, (st, msg)
+
+
+@pytest.mark.parametrize("ws,nbytes,msg", [
+    (A + 640 * MB + 8, 4096, "ws is not 16-byte aligned"),
+    (0, 4096, "ws is NULL"),
+    (A + 384 * MB, 4096, "overlaps output ws"),  # dq
+    (A, 4096, "ws overlaps input q"),
+])
+def test_bwd_workspace_validation(ws, nbytes, msg):
+    st, least, most = _lib.t2v_attn_bwd_qk_ws(
+        A, A + 64 * MB, A + 128 * MB, A + 192 * MB, A + 256 * MB, [0, 5], [0, 3], 1, 2, 128, 0.125, A + 320 * MB,
+        A + 384 * MB, A + 448 * MB, A + 512 * MB, A + 576 * MB, ws, nbytes, None)
+    assert st == INV and msg in _lib.t2v_last_error(), _lib.t2v_last_error()
+    assert (least, most) == (0, 0)
+
+
+def test_scratch_takes_what_can_be_had(monkeypatch):
+    """The binding's workspace: halved until the allocator has it, never below the least."""
+    import torch
+    asked = []
+
+    def empty(n, dtype, device):
+        asked.append(n)
+        if n > limit:
+            raise torch.cuda.OutOfMemoryError("none")
+        return n
+
+    monkeypatch.setattr(torch, "empty", empty)
+    for limit, want in ((1000, [1000]), (300, [1000, 500, 250]), (120, [1000, 500, 250, 125, 101])):
+        asked.clear()
+        assert _lib._scratch(1000, 101, "cuda", None) == want[-1] and asked == want
+    limit = 100
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        _lib._scratch(1000, 101, "cuda", None)

@@ -134,3 +134,87 @@ def test_partial_sums_share_one_buffer_and_stay_bounded(monkeypatch, capfd):
         d = (a.float() - b.float()).abs().max().item() / b.float().abs().max().item()
         assert d <= 2e-2, (n, d)
     t2v_release_cache()
+
+
+def _cross_inputs(lq, lk, heads, seed):
+    import torch
+    from paper_2607_01701_amd import attn_fwd
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v, dout = (torch.randn((n, heads, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+                     for n in (sum(lq), sum(lk), sum(lk), sum(lq)))
+    cu, ck = (np.concatenate([[0], np.cumsum(x)]).astype(np.int32) for x in (lq, lk))
+    out, lse = attn_fwd(q, k, v, cu, 0.1, cu_seqlens_k=ck)
+    return q, k, v, out, lse, dout, cu, ck
+
+
+def test_path_does_not_depend_on_what_is_in_flight():
+    """Packs that grow, enqueued without waiting (their partial sums would take 384, 480 and 576 MiB
+    at once), give bitwise what each gives on an idle GPU."""
+    import torch
+    from paper_2607_01701_amd import attn_bwd
+    log("case growing packs in flight")
+    packs = [_cross_inputs([t // 16] * 16, [200] * 16, 24, 6) for t in (100000, 140000, 170000)]
+
+    def backward(p):
+        return attn_bwd(*p[:6], p[6], 0.1, cu_seqlens_k=p[7])[1:]
+
+    torch.cuda.synchronize()
+    in_flight = [backward(p) for p in packs]
+    torch.cuda.synchronize()
+    for p, g in zip(packs, in_flight):
+        alone = backward(p)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(g, alone))
+
+
+def test_workspace_sizes_give_the_same_bits():
+    """t2v_attn_bwd_qk_ws: no workspace is refused with the sizes it could use and nothing written; the
+    least (a head at a time), an uneven one (5 of 41 heads) and the most give bitwise equal gradients and
+    never write past their size; t2v_attn_bwd_qk takes the general path."""
+    import torch
+    from paper_2607_01701_amd import _lib, attn_bwd
+    H, lq, lk = 41, [6000, 0, 700, 4099], [77, 0, 31, 256]
+    q, k, v, out, lse, dout, cu, ck = _cross_inputs(lq, lk, H, 7)
+    ws = torch.empty((2, H, sum(lq)), dtype=torch.float32, device="cuda")
+    log(f"case workspace sizes lq={lq} lk={lk} H={H}")
+
+    def call(nbytes):
+        g = [torch.full_like(x, 3.0) for x in (q, k, v)]
+        buf = torch.full((nbytes + 4096,), 77, dtype=torch.uint8, device="cuda")
+        r = _lib.t2v_attn_bwd_qk_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), cu, ck,
+                                    len(lq), H, 128, 0.1, dout.data_ptr(), *(x.data_ptr() for x in g),
+                                    ws.data_ptr(), buf.data_ptr() if nbytes else None, nbytes,
+                                    torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert bool((buf[nbytes:] == 77).all()), "written past the workspace"
+        return r, g
+
+    (st, least, most), g = call(0)
+    assert st == _lib.T2V_ERR_WORKSPACE and 0 < least and most == H * least
+    assert all(bool((x == 3.0).all()) for x in g)
+    assert call(least - 16)[0][0] == _lib.T2V_ERR_WORKSPACE
+    (st, *_), full = call(most)
+    assert st == _lib.T2V_OK
+    for nbytes in (least, 5 * least + 256):
+        (st, *_), g = call(nbytes)
+        assert st == _lib.T2V_OK and all(torch.equal(a, b) for a, b in zip(g, full)), nbytes
+    bound = attn_bwd(q, k, v, out, lse, dout, cu, 0.1, cu_seqlens_k=ck)
+    assert all(torch.equal(a, b) for a, b in zip(bound, full))
+
+
+def test_entry_without_workspace_takes_the_general_path(monkeypatch):
+    import torch
+    from paper_2607_01701_amd import _lib, attn_bwd
+    H = 41
+    q, k, v, out, lse, dout, cu, ck = _cross_inputs([6000, 4099], [77, 256], H, 8)
+    ws = torch.empty((2, H, 10099), dtype=torch.float32, device="cuda")
+    g = [torch.empty_like(x) for x in (q, k, v)]
+    log("case cross backward without workspace")
+    st = _lib.t2v_attn_bwd_qk(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), cu, ck, 2, H,
+                              128, 0.1, dout.data_ptr(), *(x.data_ptr() for x in g), ws.data_ptr(),
+                              torch.cuda.current_stream().cuda_stream)
+    assert st == 0, _lib.t2v_last_error()
+    monkeypatch.setenv("T2V_SHORT", "off")
+    want = attn_bwd(q, k, v, out, lse, dout, cu, 0.1, cu_seqlens_k=ck)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(g, want))
