@@ -48,7 +48,8 @@
  * overwrites dq. Results stay deterministic; they differ from the unsplit order only by
  * rounding. t2v_attn_bwd_qk_ws, given device memory for the partial sums, takes a one-pass
  * backward instead for cross-attention at head_dim 128 whose key segments all have at most 256
- * rows, with enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs): one kernel
+ * rows, with enough queries to fill the GPU (heads * Tq of about 330,000 on 256 CUs) and, per
+ * piece of a sequence, to be worth its fixed part (80 in the mean): one kernel
  * computes Delta, dQ, dK and dV of a piece of a sequence's queries (up to 2048, more on the
  * largest packs) and one head, and the fp32 dK / dV of its pieces are added in order. Which path a
  * call takes follows from the entry point, its offsets and sizes, and the environment below alone.

@@ -139,12 +139,17 @@ bool persistent_enabled() {
 // out and in again for the sum), so short pieces lose what the one pass saves. Measured on 116,904
 // queries x 12 heads against 32-256 keys: general path 818-839 us; one pass with pieces of 512
 // rows 680, 1,024 583-604, 1,536 543-550, 2,048 533-538, 4,096 573 (too few to balance).
+// Where the pieces are short because the sequences are, an item's fixed part outweighs what one pass
+// saves: with equal sequences at 12 and 24 heads against 16 to 256 keys, 1 query each took 0.89 to 1.21
+// of the general path's time, 33 queries 0.88 to 1.21, 65 queries 0.86 to 1.05, 90 queries 0.79 to
+// 0.96, 130 queries 0.69 to 0.81. So the pieces must have kShortMinMean queries in the mean, between
+// the last size that lost and the first that always won.
 // Above kShortMaxPieces pieces (eight per CU, which balance as well as more) the pieces grow instead:
 // cutting a segment into equal pieces at most doubles their number, so a call's partial sums stay
 // under 1 GiB (the caller's workspace).
 // Returns the piece length, or 0 for the general path. T2V_SHORT=off selects that (ablations and
 // tests). Self-attention takes the general path, which t2v_attn_bwd_noalloc shares.
-constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048, kShortMaxPieces = 2048;
+constexpr int kShortMinPiece = 512, kShortMaxPiece = 2048, kShortMaxPieces = 2048, kShortMinMean = 80;
 int short_piece(const int32_t* cu_q, const int32_t* cu_k, int nseq, int heads, int head_dim, int ncu) {
   const char* s = std::getenv("T2V_SHORT");
   if (head_dim != 128 || ncu < 1 || (s != nullptr && std::strcmp(s, "off") == 0)) return 0;
@@ -154,8 +159,15 @@ int short_piece(const int32_t* cu_q, const int32_t* cu_k, int nseq, int heads, i
   const int64_t share = 2 * static_cast<int64_t>(heads) * cu_q[nseq] / (5 * ncu);
   if (share < kShortMinPiece) return 0;
   const int64_t least = (static_cast<int64_t>(heads) * cu_q[nseq] / kShortMaxPieces + 63) / 64 * 64;
-  const int64_t piece = std::max(std::min<int64_t>(share / 64 * 64, kShortMaxPiece), least);
-  return static_cast<int>(std::min<int64_t>(piece, 1 << 30));
+  const int piece = static_cast<int>(
+      std::min<int64_t>(std::max(std::min<int64_t>(share / 64 * 64, kShortMaxPiece), least), 1 << 30));
+  int64_t pieces = 0;
+  for (int i = 0; i < nseq; ++i) {
+    int n = 1, step = 0;
+    loop_pieces(cu_q[i + 1] - cu_q[i], piece, &n, &step);
+    pieces += cu_q[i + 1] > cu_q[i] ? n : 0;
+  }
+  return cu_q[nseq] >= kShortMinMean * pieces ? piece : 0;
 }
 
 // A step of a one-pass item takes about 1.6 times as long with 129 to 256 keys as with fewer.

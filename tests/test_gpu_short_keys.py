@@ -218,3 +218,24 @@ def test_entry_without_workspace_takes_the_general_path(monkeypatch):
     want = attn_bwd(q, k, v, out, lse, dout, cu, 0.1, cu_seqlens_k=ck)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(g, want))
+
+
+@pytest.mark.parametrize("lq,lk,one_pass", [
+    ([33] * 300, [16] * 300, False), ([79] * 150, [200] * 150, False), ([80] * 150, [200] * 150, True),
+    ([1] * 200 + [12000, 0], [31] * 201 + [0], False), ([1] * 150 + [20000, 0], [31] * 151 + [0], True),
+], ids=["33_queries", "79_queries", "80_queries", "ones_and_one_long", "ones_and_one_longer"])
+def test_short_query_sequences_keep_the_general_path(lq, lk, one_pass, capfd, monkeypatch):
+    """With pieces of fewer than 80 queries in the mean an item's fixed part outweighs the saved pass."""
+    import torch
+    from paper_2607_01701_amd import attn_bwd, t2v_release_cache
+    H = 40
+    cu, ck = (np.concatenate([[0], np.cumsum(x)]).astype(np.int32) for x in (lq, lk))
+    x, y = (torch.zeros((n, H, 128), dtype=torch.bfloat16, device="cuda") for n in (sum(lq), sum(lk)))
+    lse = torch.zeros((H, sum(lq)), dtype=torch.float32, device="cuda")
+    log(f"case path of short query sequences n={len(lq)} lq={lq[0]}")
+    t2v_release_cache()
+    monkeypatch.setenv("T2V_LOG", "1")
+    attn_bwd(x, y, y, x, lse, x, cu, 0.1, cu_seqlens_k=ck)
+    torch.cuda.synchronize()
+    lists = capfd.readouterr().err.count("t2v: work list")
+    assert lists == (1 if one_pass else 2)  # the general path has one for dK/dV and one for dQ
