@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_bwd_dkdv_wide_kernel(
         for (int i = 0; i < 4; ++i) {
           bf16x4 w;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = static_cast<bf16>(acc[b2][db][4 * i + e] * m);
+          for (int e = 0; e < 4; ++e) w[e] = static_cast<bf16>(acc_read(acc[b2][db][4 * i + e]) * m);
           *reinterpret_cast<bf16x4*>(tile + swz_off<64>(db * 32 + (el & 31), b2 * 32 + 8 * i + 4 * eg)) = w;
         }
     bf16* const g = (which == 0 ? dk : dv) + base;

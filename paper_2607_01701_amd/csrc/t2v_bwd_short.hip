@@ -321,7 +321,7 @@ T2V_DEV void short_item(const ShortArgs& a, const Item& it, Lds& lds) {
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          rows[(b * 32 + (r >> 2) * 8 + (el >> 5) * 4 + (r & 3)) * D + db * 32 + (el & 31)] = acc[b][db][r];
+          rows[(b * 32 + (r >> 2) * 8 + (el >> 5) * 4 + (r & 3)) * D + db * 32 + (el & 31)] = acc_read(acc[b][db][r]);
     const int c4 = (el & 31) * 4;
     const float m = which == 0 ? a.scale : 1.0f;
     float* slot = a.partial + static_cast<int64_t>(max(it.slot, 0)) * (2 * kKeys * D) + which * kKeys * D;

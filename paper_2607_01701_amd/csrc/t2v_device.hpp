@@ -336,11 +336,18 @@ T2V_DEV void pin(bf16x8& x) { asm volatile("" : "+v"(x)); }
 // and scores have all 256 VGPRs. The compiler does not look into the assembly for hazards: the
 // s_nop covers the two wait states between a VALU write of a or b and the MFMA that reads it
 // (it issues while the previous MFMA runs), MFMAs on one accumulator interlock in hardware, and
-// acc_settle() must precede the first ordinary read of the accumulators.
+// acc_settle() waits out the last ones before acc_read() takes the sums; both are volatile, which
+// keeps them in that order. (An ordinary read is a register copy that the compiler may move above
+// the wait.) Nothing may copy an accumulator in between: the tests check the generated code.
 T2V_DEV void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
   asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 T2V_DEV void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+T2V_DEV float acc_read(float acc) {  // one element of an accumulator
+  float x;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc));
+  return x;
+}
 
 // Lane of the wave, computed afresh so that it need not stay in a register.
 T2V_DEV int lane_again() {
