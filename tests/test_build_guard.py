@@ -65,10 +65,10 @@ def test_clean_kernel_passes(tmp_path):
 
 
 def test_attention_kernels_are_spill_free(tmp_path):
-    """Every kernel of the four attention sources reports no spills and no scratch (the same
-    check the build applies)."""
+    """Every kernel of the attention sources reports no spills and no scratch (the same check the
+    build applies)."""
     names = {}
-    for src in ("t2v_fwd.hip", "t2v_bwd_pre.hip", "t2v_bwd_dkdv.hip", "t2v_bwd_dq.hip"):
+    for src in [s for s in B.HIP_SOURCES if s.startswith(("t2v_fwd", "t2v_bwd"))]:
         cmd = [B.HIPCC, *B.HIP_FLAGS, *B.SCHED.get(src, []), *B.RESOURCE_REMARKS, "-c", os.path.join(B.CSRC, src),
                "-o", str(tmp_path / (src + ".o"))]
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
@@ -76,7 +76,8 @@ def test_attention_kernels_are_spill_free(tmp_path):
         res = B.kernel_resources(r.stdout)
         assert not B.resource_violations(res), B.resource_violations(res)
         names.update(res)
-    for kern in ("attn_fwd_kernel", "attn_bwd_pre_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dq_kernel"):
+    for kern in ("attn_fwd_kernel", "attn_bwd_pre_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dkdv_wide_kernel",
+                 "attn_bwd_dq_kernel", "attn_bwd_short_kernel", "short_reduce_kernel"):
         assert any(kern in n for n in names), kern
 
 
