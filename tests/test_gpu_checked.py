@@ -2,7 +2,8 @@
 list checked on the host against cu_seqlens and every row the kernels copy into LDS checked
 on the device against its clip). On packs that reach every kernel form (edge lengths, several
 tiles, empty clips, head_dim 64 and 128, narrow and wide tiles, cross-attention with the
-dK/dV loop split, the persistent grid, the no-allocation backward) every call returns T2V_OK,
+dK/dV loop split and with the one-pass backward, the persistent grid, the no-allocation backward)
+every call returns T2V_OK,
 so no work item and no copied row leaves its clip, and every output equals the product
 library's bitwise. With the canary (bounds taken one row short) the kernels' checks report,
 and the next call without it is clean again."""
@@ -31,10 +32,13 @@ PACKS = [
     ("cross_d128", lambda: make_pack_qk([1000, 5, 2000, 129], [256, 3, 77, 600], 2, 128, seed=65)),
     # short key segments against long query segments: the dK/dV loops are split into pieces
     ("cross_split_d128", lambda: make_pack_qk([9000, 300, 4500, 0, 2600], [100, 50, 256, 0, 1], 2, 128, seed=66)),
+    # enough queries for the one-pass backward (pieces, several LDS stages, 1 to 256 keys)
+    ("cross_one_pass", lambda: make_pack_qk([3000, 1, 31, 33, 0, 96, 97, 2049, 1500, 65],
+                                            [1, 32, 33, 128, 0, 129, 256, 255, 64, 100], 64, 128, seed=70)),
     ("cross_split_d64", lambda: make_pack_qk([7000, 2100, 65], [33, 500, 129], 3, 64, seed=67)),
 ]
 MODES = [("default", {}), ("narrow", {"T2V_QTILE": "narrow"}), ("wide", {"T2V_QTILE": "wide"}),
-         ("persistent", {"T2V_PERSISTENT": "1"})]
+         ("wide_keys", {"T2V_KVTILE": "wide"}), ("persistent", {"T2V_PERSISTENT": "1"})]
 
 
 @pytest.mark.parametrize("mode,env", MODES, ids=[m[0] for m in MODES])
@@ -97,3 +101,29 @@ def test_canary_makes_the_kernel_checks_report(monkeypatch):
         assert "dK/dV kernel" in str(e.value) or "dQ kernel" in str(e.value), str(e.value)
         monkeypatch.delenv("T2V_CHECK_CANARY")
         attn_bwd(d["q"], d["k"], d["v"], out, lse, d["dout"], pack.cu_seqlens, pack.scale)
+
+
+@pytest.mark.parametrize("kernel", ["dK/dV", "one-pass backward"])
+def test_canary_reaches_the_other_backward_kernels(kernel, monkeypatch):
+    """The same for the 64-keys-per-wave dK/dV kernel and the one-pass backward."""
+    from paper_2607_01701_amd import attn_bwd, attn_fwd
+    if kernel == "dK/dV":
+        monkeypatch.setenv("T2V_KVTILE", "wide")
+        pack = make_pack([70, 300], 2, 128, seed=71)
+    else:
+        pack = make_pack_qk([4097, 3000], [77, 256], 64, 128, seed=72)
+    d = dev_inputs(pack)
+    log(f"case checked library: canary, {kernel}")
+
+    def backward():
+        attn_bwd(d["q"], d["k"], d["v"], out, lse, d["dout"], pack.cu_seqlens, pack.scale,
+                 cu_seqlens_k=pack.cu_seqlens_k)
+
+    with _lib.use_checked_library():
+        out, lse = attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, cu_seqlens_k=pack.cu_seqlens_k)
+        monkeypatch.setenv("T2V_CHECK_CANARY", "1")
+        with pytest.raises(_lib.T2VError) as e:
+            backward()
+        assert e.value.status == _lib.T2V_ERR_BOUNDS and f"{kernel} kernel" in str(e.value), str(e.value)
+        monkeypatch.delenv("T2V_CHECK_CANARY")
+        backward()

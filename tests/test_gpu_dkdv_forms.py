@@ -62,3 +62,33 @@ def test_form_is_chosen_from_the_pack(heads, lens, rows, capfd, monkeypatch):
     err = capfd.readouterr().err
     log(f"case form choice heads={heads} lens={lens[:2]}")
     assert err.splitlines()[0].split("heads, ")[1].startswith(f"{rows}-row tiles"), err
+
+
+@pytest.mark.parametrize("case,scale,order", [("negative_scale", -0.2, None), ("zero_scale", 0.0, None),
+                                              ("pack_order", 0.1, "natural"), ("special_values", 0.1, None)])
+def test_wide_form_on_other_scales_orders_and_values(case, scale, order, monkeypatch):
+    """Bitwise equal there too; NaN and infinities come out where the other form has them."""
+    import torch
+    pack = make_pack_qk([300, 129, 160], [300, 257, 64], 2, 128, seed=82)
+    log(f"case dK/dV forms {case}")
+    d = dev_inputs(pack)
+    if case == "special_values":
+        d["q"][40, 0, 3] = float("nan")
+        d["dout"][305, 1, 7] = float("inf")
+        d["v"][560, 0, 0] = -float("inf")
+    if order is not None:
+        monkeypatch.setenv("T2V_ORDER", order)
+    monkeypatch.setenv("T2V_KVTILE", "narrow")
+    a = {k: v.clone() for k, v in run_hip(pack, d, scale).items()}
+    monkeypatch.setenv("T2V_KVTILE", "wide")
+    b = run_hip(pack, d, scale)
+    for k in a:
+        assert bool(((a[k] == b[k]) | (a[k].isnan() & b[k].isnan())).all()), k
+    if case == "special_values":
+        assert bool(a["dk"][:300, 0].isnan().all()) and not bool(a["dk"][:300, 1].isnan().any())
+        assert not bool(a["dv"][300:557, 1, 7].isfinite().all()) and not bool(a["dk"][557:, 0].isfinite().all())
+    else:
+        ref = oracle.attention(pack.f32("q"), pack.f32("k"), pack.f32("v"), pack.f32("dout"), pack.cu_seqlens, scale,
+                               cu_seqlens_k=pack.cu_seqlens_k)
+        errs, _ = compare_full(to_np(b), ref, pack.cu_seqlens, "wide dK/dV", cu_k=pack.cu_seqlens_k)
+        assert_within(errs)

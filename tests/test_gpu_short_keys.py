@@ -239,3 +239,49 @@ def test_short_query_sequences_keep_the_general_path(lq, lk, one_pass, capfd, mo
     torch.cuda.synchronize()
     lists = capfd.readouterr().err.count("t2v: work list")
     assert lists == (1 if one_pass else 2)  # the general path has one for dK/dV and one for dQ
+
+
+@pytest.mark.parametrize("case,scale", [("negative_scale", -0.2), ("zero_scale", 0.0), ("special_values", 0.1)])
+def test_other_scales_orders_and_values(case, scale, monkeypatch):
+    """The one-pass backward on negative and zero scales against the oracle; NaN and infinities come out
+    where the general path has them, and leave the other sequences and heads as they were; pack
+    order changes nothing."""
+    import torch
+    from paper_2607_01701_amd import attn_bwd, attn_fwd
+    lq, lk, H = [3000, 2049, 96], [77, 256, 33], 65
+    pack = make_pack_qk(lq, lk, H, 128, seed=93)
+    log(f"case one-pass backward {case}")
+    d = dev_inputs(pack)
+
+    def backward(**env):
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
+        out, lse = attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, scale, cu_seqlens_k=pack.cu_seqlens_k)
+        g = attn_bwd(d["q"], d["k"], d["v"], out, lse, d["dout"], pack.cu_seqlens, scale, cu_seqlens_k=pack.cu_seqlens_k)
+        torch.cuda.synchronize()
+        for name in env:
+            monkeypatch.delenv(name)
+        return dict(zip(("dq", "dk", "dv"), g))
+
+    clean = backward()
+    for n, x in backward(T2V_ORDER="natural").items():
+        assert torch.equal(x, clean[n]), n
+    if case != "special_values":
+        heads = [0, H - 1]
+        f = {n: bf16_bits_to_f32(np.ascontiguousarray(getattr(pack, n)[:, heads])) for n in ("q", "k", "v", "dout")}
+        ref = oracle.attention(f["q"], f["k"], f["v"], f["dout"], pack.cu_seqlens, scale, cu_seqlens_k=pack.cu_seqlens_k)
+        assert_within({"out": 0.0, "lse": 0.0, **{n: rel_err(x[:, heads].double().cpu().numpy(), ref[n])
+                                                  for n, x in clean.items()}})
+        return
+    d["q"][40, 0, 3] = float("nan")        # sequence 0, head 0
+    d["dout"][3005, 1, 7] = float("inf")   # sequence 1, head 1
+    d["k"][340, 2, 0] = float("nan")       # sequence 2, head 2
+    a, g = backward(), backward(T2V_SHORT="off")
+    for n in a:
+        assert torch.equal(a[n].isnan(), g[n].isnan()) and torch.equal(a[n].isinf(), g[n].isinf()), n
+        same = a[n] == clean[n]
+        c = np.cumsum([0] + (lq if n == "dq" else lk))
+        for s in range(3):
+            rest = [h for h in range(H) if h != s]
+            assert bool(same[c[s]:c[s + 1], rest].all()), (n, s)
+    assert bool(a["dk"][:77, 0].isnan().all()) and bool(a["dq"][5049:, 2].isnan().all())
