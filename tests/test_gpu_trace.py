@@ -68,3 +68,23 @@ def test_trace_overflow_runs_untraced(monkeypatch):
     finally:
         _lib.t2v_trace_set(None, 0)
     assert (n, over) == (nf, 2)
+
+
+def test_balance_report_traces_every_item(monkeypatch):
+    """bench.py --balance sizes its trace from the tiles that it forces: 256 keys in the dK/dV kernel,
+    which a pack like this one takes by itself."""
+    import os
+    from types import SimpleNamespace
+    import bench
+    from paper_2607_01701_amd import workload
+    cu = np.arange(9, dtype=np.int32) * 4096
+    zeros = np.zeros((cu[-1], 24, 128), dtype=np.uint16)
+    pack = SimpleNamespace(heads=24, head_dim=128, total_tokens=int(cu[-1]), cu_seqlens=cu, scale=0.1, q=zeros, k=zeros,
+                           v=zeros, dout=zeros)
+    monkeypatch.setattr(workload, "make_workload", lambda name, seed=0: pack)
+    log("case balance report")
+    before = dict(os.environ)
+    report = bench.balance_report("uniform")
+    assert dict(os.environ) == before
+    rows = [x.split() for x in report.splitlines() if x.startswith(("longest_first", "natural"))]
+    assert [(r[1], int(r[2])) for r in rows] == [(k, 24 * 8 * 16) for k in ("fwd", "bwd_dkdv", "bwd_dq")] * 2
