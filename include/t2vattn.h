@@ -264,7 +264,8 @@ int t2v_plan_cascades(int n_cascades, const int32_t* pred_ptr, const int32_t* pr
 /* Per-kernel timing, for measurement. While enabled, every kernel launch is bracketed by
  * two HIP events recorded on the launch stream. t2v_kernel_times waits for the recorded
  * events, returns the summed elapsed milliseconds and the launch count of each kernel since
- * the previous read (slots: 0 forward, 1 backward Delta, 2 backward dK/dV, 3 backward dQ),
+ * the previous read (slots: 0 forward, 1 backward Delta, 2 backward dK/dV, 3 backward dQ; the
+ * one-pass backward with its reduce counts as 2, once per batch of heads),
  * and forgets them. Enabling or disabling also forgets. Calls overlapping with launches on
  * other host threads are serialised by a mutex.
  *   ms_out     host double[4];  counts_out host int[4] */
@@ -276,7 +277,7 @@ int t2v_kernel_times(double* ms_out, int* counts_out);
  * variation. While armed, every forward, dK/dV and dQ kernel launch takes the next n_items
  * records of dev_records, one per workgroup in work-list order, each four uint64:
  * {CU id, start, end, kernel slot}; CU id = (XCC_ID << 16) | bits 8..15 of HW_ID, start
- * and end on the constant 100 MHz device clock, slot 0 forward, 2 dK/dV, 3 dQ. A launch
+ * and end on the constant 100 MHz device clock, slot 0 forward, 2 dK/dV or one-pass, 3 dQ. A launch
  * whose records do not fit runs untraced and is counted as overflowed. Tracing does not
  * change any result.
  *   dev_records  device unsigned long long[4 * capacity], 8-byte aligned, caller-owned;
