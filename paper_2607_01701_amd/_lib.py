@@ -296,8 +296,9 @@ def _stream_handle(stream):
     import torch
     if stream is not None:
         return stream.cuda_stream
-    # torch.cuda.current_stream().cuda_stream without building the Stream object (3 us a call).
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # The handle without building the Stream object (3 us a call), where torch has this private function.
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _scratch(most: int, least: int, device, stream):

@@ -436,3 +436,12 @@ def test_scratch_takes_what_can_be_had(monkeypatch):
     limit = 100
     with pytest.raises(torch.cuda.OutOfMemoryError):
         _lib._scratch(1000, 101, "cuda", None)
+
+
+def test_stream_handle_without_the_private_function(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1234))
+    assert _lib._stream_handle(None) == 0x1234
+    assert _lib._stream_handle(SimpleNamespace(cuda_stream=0x5678)) == 0x5678
