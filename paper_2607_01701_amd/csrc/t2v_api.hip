@@ -308,6 +308,10 @@ class ListPool {
       c.base = nullptr;
       c.alloc = RangeAllocator(0);  // an empty slot: indices of live blocks stay valid
     }
+    // The next chunk follows the size of those that are left, not of those that were freed.
+    last_size_ = 0;
+    for (auto& c : chunks_) last_size_ = std::max(last_size_, c.alloc.size());
+    if (last_size_ == 0) chunks_.clear();
     for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     events_.clear();
   }
@@ -352,7 +356,7 @@ class ListPool {
     }
   }
   bool pinned_;
-  uint64_t last_size_ = 0;  // size of the newest chunk: the next one doubles it
+  uint64_t last_size_ = 0;  // size of the largest chunk: the next one doubles it
   std::vector<Chunk> chunks_;
   std::list<Pending> pending_;
   std::vector<hipEvent_t> events_;

@@ -189,3 +189,19 @@ def test_fresh_packs_on_concurrent_streams_reuse_list_memory():
     torch.cuda.synchronize()
     bad = [i for i in range(len(packs)) if not same(alone[i], results[i])]
     assert not bad, f"{len(bad)} packs differ from their single-stream result, first {packs[bad[0]]}"
+
+
+def test_released_list_memory_does_not_grow():
+    """t2v_release_cache gives the pools' memory back, and the next list starts small again."""
+    import torch
+    from paper_2607_01701_amd import attn_fwd, t2v_release_cache
+    pack = make_pack([100, 37], 2, 64, seed=92)
+    d = dev_inputs(pack)
+    out, lse = attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale)
+    log("case 8 releases of the work lists")
+    for _ in range(8):  # doubling each time would make the last chunk 1 GiB
+        t2v_release_cache()
+        free = torch.cuda.mem_get_info()[0]
+        attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, out=out, lse=lse)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)
