@@ -301,11 +301,18 @@ def _stream_handle(stream):
     return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
+def _on(stream):
+    """Allocations inside belong to `stream` (None: the current one), so that scratch which only work on
+    that stream uses can be dropped as soon as the work is enqueued."""
+    import torch
+    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+
+
 def _scratch(most: int, least: int, device, stream):
     """Device memory for one call on `stream`: `most` bytes, or as many as can be had by halving down
-    to `least`. It belongs to that stream, so it can be dropped as soon as the call has returned."""
+    to `least`."""
     import torch
-    with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
+    with _on(stream):
         while True:
             try:
                 return torch.empty(most, dtype=torch.uint8, device=device)
@@ -401,7 +408,8 @@ def attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=None
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(k) if dv is None else dv
     if delta_ws is None:
-        delta_ws = torch.empty((2, H, T), dtype=torch.float32, device=q.device)
+        with _on(stream):
+            delta_ws = torch.empty((2, H, T), dtype=torch.float32, device=q.device)
     _check_tensor(dq, "dq", (T, H, D))
     _check_tensor(dk, "dk", (Tk, H, D))
     _check_tensor(dv, "dv", (Tk, H, D))

@@ -445,3 +445,32 @@ def test_stream_handle_without_the_private_function(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1234))
     assert _lib._stream_handle(None) == 0x1234
     assert _lib._stream_handle(SimpleNamespace(cuda_stream=0x5678)) == 0x5678
+
+
+def test_scratch_of_a_call_belongs_to_its_stream(monkeypatch):
+    """delta_ws is dropped when attn_bwd returns, with the kernels still running: it is allocated on the
+    stream they run on, so that no other stream is given its memory meanwhile."""
+    import contextlib
+    import torch
+    inside, seen = [], {}
+
+    @contextlib.contextmanager
+    def stream_context(s):
+        inside.append(s)
+        yield
+        inside.pop()
+
+    empty = torch.empty
+
+    def recorded(shape, **kw):
+        seen[tuple(shape)] = list(inside)
+        return empty(shape, **kw)
+
+    monkeypatch.setattr(torch.cuda, "stream", stream_context)
+    monkeypatch.setattr(torch, "empty", recorded)
+    x = _cpu((10, 2, 128))
+    lse = _cpu((2, 10), torch.float32)
+    for stream in ("another stream", None):
+        with pytest.raises(ValueError, match="must be a CUDA tensor"):
+            _lib.attn_bwd(x, x, x, x, lse, x, [0, 10], 0.1, stream=stream)
+        assert seen[2, 2, 10] == ([] if stream is None else [stream])
