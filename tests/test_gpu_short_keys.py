@@ -285,3 +285,32 @@ def test_other_scales_orders_and_values(case, scale, monkeypatch):
             rest = [h for h in range(H) if h != s]
             assert bool(same[c[s]:c[s + 1], rest].all()), (n, s)
     assert bool(a["dk"][:77, 0].isnan().all()) and bool(a["dq"][5049:, 2].isnan().all())
+
+
+def test_captured_call_gives_the_same_bits():
+    """A backward call captured into a graph takes the same path as an eager one: each replay, with eager
+    calls between, writes what the eager call wrote."""
+    import torch
+    from paper_2607_01701_amd import attn_bwd
+    log("case captured one-pass backward")
+    q, k, v, out, lse, dout, cu, ck = _cross_inputs([6000, 4099], [77, 256], 41, 9)
+    grads = [torch.empty_like(x) for x in (q, k, v)]
+    ws = torch.empty((2, 41, 10099), dtype=torch.float32, device="cuda")
+
+    def backward():
+        attn_bwd(q, k, v, out, lse, dout, cu, 0.1, *grads, delta_ws=ws, cu_seqlens_k=ck)
+
+    backward()
+    torch.cuda.synchronize()
+    want = [x.clone() for x in grads]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        backward()
+    for i in range(4):
+        for x in grads:
+            x.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(grads, want)), f"replay {i}"
+        backward()
+        assert all(torch.equal(a, b) for a, b in zip(grads, want)), f"eager call after replay {i}"
