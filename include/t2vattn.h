@@ -32,6 +32,8 @@
  * comes from pooled device and pinned chunks; a released list's memory is
  * reused only after the launches that read it have finished (events recorded
  * on their streams), so no call waits for the device. t2v_release_cache releases them.
+ * A call on a stream that is being captured works as any other, and its work lists are kept for
+ * the graph: a graph may be replayed until t2v_release_cache is called.
  *
  * Tiles. The forward and dQ kernels own 256-query tiles (8 waves, one workgroup per CU)
  * or 128-query tiles (4 waves, two or three per CU): narrow tiles at head_dim 64, and at
@@ -211,7 +213,8 @@ int t2v_attn_bwd_qk_ws(const void* q, const void* k, const void* v,
 /* Thread-local message describing the last non-OK status of this thread. */
 const char* t2v_last_error(void);
 
-/* Waits for the device, then frees every cached work list. Safe to call at any time. */
+/* Waits for the device, then frees every cached work list, those of captured graphs too (which must
+ * not be replayed after it). Safe to call at any time. */
 void t2v_release_cache(void);
 
 /* Host-only scheduler, exposed for testing. Builds the work list the kernels use for

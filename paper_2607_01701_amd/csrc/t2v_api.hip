@@ -209,6 +209,41 @@ bool fail_alloc_for_test() {
   return s != nullptr && std::strcmp(s, "1") == 0;
 }
 
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+// While it lives (and `on`), this thread's calls that no graph records are allowed during a capture.
+class RelaxedCapture {
+ public:
+  explicit RelaxedCapture(bool on) : on_(on) {
+    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  ~RelaxedCapture() {
+    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+
+ private:
+  bool on_;
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
+// A copy to the device on a stream of its own, finished on return.
+hipError_t upload_now(void* dst, const void* src, size_t bytes) {
+  hipStream_t s = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e != hipSuccess) return e;
+  e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+  const hipError_t done = hipStreamSynchronize(s);
+  (void)hipStreamDestroy(s);
+  return e != hipSuccess ? e : done;
+}
+
 // cu_seqlens must be host memory: the scheduler reads it on the host.
 int check_host_pointer(const int32_t* cu) {
   hipPointerAttribute_t attr;
@@ -280,6 +315,12 @@ class ListPool {
     pending_.push_back({b, std::move(events)});
   }
 
+  // Caller holds mu(). A captured graph may read the block at any time: it is kept until the next
+  // trim_after_sync().
+  void keep(const Block& b) {
+    if (b.chunk >= 0) kept_.push_back(b);
+  }
+
   // Caller holds mu(). An event from the pool (or a new one), for recording.
   hipError_t take_event(hipEvent_t* ev) {
     if (!events_.empty()) {
@@ -299,6 +340,8 @@ class ListPool {
   // its chunk), and the idle events.
   void trim_after_sync() {
     reclaim();
+    for (const Block& b : kept_) (void)chunks_[b.chunk].alloc.release(b.off, b.bytes);
+    kept_.clear();
     for (auto& c : chunks_) {
       if (c.base == nullptr || c.alloc.free_bytes() != c.alloc.size()) continue;
       if (pinned_)
@@ -359,6 +402,7 @@ class ListPool {
   uint64_t last_size_ = 0;  // size of the largest chunk: the next one doubles it
   std::vector<Chunk> chunks_;
   std::list<Pending> pending_;
+  std::vector<Block> kept_;
   std::vector<hipEvent_t> events_;
 };
 
@@ -413,6 +457,7 @@ struct Plan {
   ListPool::Block mem;             // d_items' block in the device pool
   hipEvent_t ready = nullptr;      // upload finished (from the device pool's event pool)
   std::vector<std::pair<hipStream_t, hipEvent_t>> uses;  // last launch reading d_items, per stream
+  bool captured = false;  // a captured graph's launches read d_items
 #if T2V_CHECKED
   std::vector<Item> host_items;  // checked builds: the list as uploaded, validated at every call
 #endif
@@ -422,16 +467,26 @@ struct Plan {
     std::vector<hipEvent_t> evs;
     if (ready != nullptr) evs.push_back(ready);
     for (auto& u : uses) evs.push_back(u.second);
+    if (captured) {
+      p.dev.keep(mem);
+      mem = ListPool::Block{};
+    }
     p.dev.release_after(mem, std::move(evs));
   }
 };
 using PlanRef = std::shared_ptr<Plan>;
 
 // Records, on `stream`, the point after which the launches just enqueued no longer read the
-// plan's list. Later launches on the same stream replace the earlier event (stream order).
+// plan's list. Later launches on the same stream replace the earlier event (stream order). Captured
+// launches run whenever their graph does: the list is then kept until t2v_release_cache.
 int note_use(const PlanRef& plan, hipStream_t stream) {
+  const bool capturing = is_capturing(stream);
   DevicePools& p = pools(plan->device);
   std::lock_guard<std::mutex> lock(p.mu);
+  if (capturing) {
+    plan->captured = true;
+    return T2V_OK;
+  }
   hipEvent_t ev = nullptr;
   hipError_t e = p.dev.take_event(&ev);
   if (e == hipSuccess) e = hipEventRecord(ev, stream);
@@ -523,6 +578,8 @@ class PlanCache {
       std::fprintf(stderr, "\n");
     }
     if (bytes > 0) {
+      const bool capturing = is_capturing(stream);
+      const RelaxedCapture relaxed(capturing);  // for the pools' allocations and the upload
       DevicePools& dp = pools(device);
       std::lock_guard<std::mutex> plock(dp.mu);
       ListPool::Block staging;
@@ -534,20 +591,28 @@ class PlanCache {
       }
       p->d_items = static_cast<Item*>(p->mem.ptr);
       std::memcpy(staging.ptr, items.data(), bytes);
-      e = hipMemcpyAsync(p->d_items, staging.ptr, bytes, hipMemcpyHostToDevice, stream);
-      hipEvent_t copied = nullptr;
-      if (e == hipSuccess) e = dp.pin.take_event(&copied);
-      if (e == hipSuccess) e = hipEventRecord(copied, stream);
-      if (e != hipSuccess) {
-        if (copied != nullptr) (void)hipEventDestroy(copied);
-        (void)hipStreamSynchronize(stream);  // the staging block may still be read
+      if (capturing) {
+        // Now, outside the graph: an eager call that finds the plan before the graph has run would
+        // otherwise read a list that is not there yet.
+        e = upload_now(p->d_items, staging.ptr, bytes);
         dp.pin.release_after(staging, {});
-        return hip_fail(e, "upload of the work list");
+        if (e != hipSuccess) return hip_fail(e, "upload of the work list");
+      } else {
+        e = hipMemcpyAsync(p->d_items, staging.ptr, bytes, hipMemcpyHostToDevice, stream);
+        hipEvent_t copied = nullptr;
+        if (e == hipSuccess) e = dp.pin.take_event(&copied);
+        if (e == hipSuccess) e = hipEventRecord(copied, stream);
+        if (e != hipSuccess) {
+          if (copied != nullptr) (void)hipEventDestroy(copied);
+          (void)hipStreamSynchronize(stream);  // the staging block may still be read
+          dp.pin.release_after(staging, {});
+          return hip_fail(e, "upload of the work list");
+        }
+        dp.pin.release_after(staging, {copied});
+        e = dp.dev.take_event(&p->ready);
+        if (e == hipSuccess) e = hipEventRecord(p->ready, stream);
+        if (e != hipSuccess) return hip_fail(e, "hipEventRecord of the work-list upload");
       }
-      dp.pin.release_after(staging, {copied});
-      e = dp.dev.take_event(&p->ready);
-      if (e == hipSuccess) e = hipEventRecord(p->ready, stream);
-      if (e != hipSuccess) return hip_fail(e, "hipEventRecord of the work-list upload");
     }
     plans_.push_front(p);
     *out = p;
@@ -1006,6 +1071,32 @@ int scratch_address(int device, unsigned char** out) {
   return T2V_OK;
 }
 
+struct HostLists {
+  std::vector<Item> kv, ql;
+};
+
+// Host lists that captured graphs copy from.
+class CapturedLists {
+ public:
+  void keep(std::shared_ptr<HostLists> l) {
+    std::lock_guard<std::mutex> lock(mu_);
+    lists_.push_back(std::move(l));
+  }
+  void clear() {
+    std::lock_guard<std::mutex> lock(mu_);
+    lists_.clear();
+  }
+
+ private:
+  std::mutex mu_;
+  std::vector<std::shared_ptr<HostLists>> lists_;
+};
+
+CapturedLists& captured_lists() {
+  static CapturedLists* c = new CapturedLists();  // never destroyed
+  return *c;
+}
+
 int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const void* out, const float* lse,
                           const int32_t* cu, int nseq, int heads, int head_dim, float scale, const void* dout,
                           void* dq, void* dk, void* dv, void* stream) {
@@ -1033,7 +1124,8 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
   int chunk = 0;
   if (split_enabled()) chunk = choose_loop_split(cu, cu, nseq, heads, kv_rows, ncu, tb / dkdv_partial_slot_bytes(head_dim)).chunk;
   const TileRule kv_rule = dkdv_rule(head_dim, chunk, persistent_enabled());
-  std::vector<Item> kv;
+  const auto lists = std::make_shared<HostLists>();
+  std::vector<Item>&kv = lists->kv, &ql = lists->ql;
   const int kv_block = rows_of(kv_rule, cu, cu, nseq, heads, order, ncu, &kv);
   if (kv.empty()) kv = build_worklist(cu, cu, nseq, heads, kv_block, order, chunk);
   const int n_kv = static_cast<int>(kv.size());
@@ -1044,7 +1136,6 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
     kv.insert(kv.end(), red.begin(), red.end());
   }
   const TileRule qr = dq_rule(head_dim);
-  std::vector<Item> ql;
   const int q_rows = rows_of(qr, cu, cu, nseq, heads, order, ncu, &ql);
   if (ql.empty()) ql = build_worklist(cu, cu, nseq, heads, q_rows, order);
 #if T2V_CHECKED
@@ -1064,7 +1155,9 @@ int attn_bwd_noalloc_impl(const void* q, const void* k, const void* v, const voi
   Item* d_kv = reinterpret_cast<Item*>(base + delta_bytes);
   Item* d_q = reinterpret_cast<Item*>(base + delta_bytes + kv_bytes);
   // Pageable sources: the runtime stages them itself, in stream order (the call returns once
-  // the host arrays may be released).
+  // the host arrays may be released). A graph copies them again on each replay, so under capture they
+  // stay where they are until t2v_release_cache.
+  if (is_capturing(s)) captured_lists().keep(lists);
   if (!kv.empty()) e = hipMemcpyAsync(d_kv, kv.data(), kv.size() * sizeof(Item), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && !ql.empty()) e = hipMemcpyAsync(d_q, ql.data(), ql.size() * sizeof(Item), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "upload of the work lists into the no-allocation scratch");
@@ -1262,6 +1355,7 @@ int t2v_trace_count(int64_t* n_records, int* n_overflowed) {
 void t2v_release_cache(void) {
   (void)hipDeviceSynchronize();
   t2v::cache().clear();
+  t2v::captured_lists().clear();
   t2v::trim_pools_after_sync();
 }
 
