@@ -32,8 +32,9 @@
  * comes from pooled device and pinned chunks; a released list's memory is
  * reused only after the launches that read it have finished (events recorded
  * on their streams), so no call waits for the device. t2v_release_cache releases them.
- * A call on a stream that is being captured works as any other, and its work lists are kept for
- * the graph: a graph may be replayed until t2v_release_cache is called.
+ * A call on a stream that is being captured works as any other (it waits on the host for the
+ * upload of its lists, which no graph repeats), and its work lists are kept for the graph: a graph may
+ * be replayed until t2v_release_cache is called.
  *
  * Tiles. The forward and dQ kernels own 256-query tiles (8 waves, one workgroup per CU)
  * or 128-query tiles (4 waves, two or three per CU): narrow tiles at head_dim 64, and at

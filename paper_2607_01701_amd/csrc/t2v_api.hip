@@ -522,7 +522,7 @@ class PlanCache {
     hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     std::list<PlanRef> evicted;  // declared before the lock: released after it
-    std::lock_guard<std::mutex> lock(mu_);
+    std::unique_lock<std::mutex> lock(mu_);
     for (auto itr = plans_.begin(); itr != plans_.end(); ++itr) {
       Plan& p = **itr;
       if (p.heads == heads && p.rule.same(rule) && p.order == order && p.device == device && p.chunk == chunk &&
@@ -530,12 +530,18 @@ class PlanCache {
           std::memcmp(p.cu.data(), cu, sizeof(int32_t) * (nseq + 1)) == 0 &&
           std::memcmp(p.cu_loop.data(), cu_loop, sizeof(int32_t) * (nseq + 1)) == 0) {
         plans_.splice(plans_.begin(), plans_, itr);  // most recently used first
-        if (p.ready != nullptr) {
-          e = hipStreamWaitEvent(stream, p.ready, 0);
-          if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
-        }
         *out = *itr;
-        return T2V_OK;
+        if (p.ready == nullptr) return T2V_OK;
+        if (is_capturing(stream)) {
+          // The graph's launches would not wait for an event recorded outside it: the upload, queued
+          // on another stream, is waited for here.
+          lock.unlock();  // *out keeps the plan
+          const RelaxedCapture relaxed(true);
+          e = hipEventSynchronize(p.ready);
+          return e == hipSuccess ? T2V_OK : hip_fail(e, "hipEventSynchronize");
+        }
+        e = hipStreamWaitEvent(stream, p.ready, 0);
+        return e == hipSuccess ? T2V_OK : hip_fail(e, "hipStreamWaitEvent");
       }
     }
     PlanRef p = std::make_shared<Plan>();

@@ -64,3 +64,39 @@ def test_replays_after_other_packs(noalloc, warm):
         torch.cuda.synchronize()
         assert all(torch.equal(r[k], want[k]) for k in want), f"replay {i}"
     t2v_release_cache()
+
+
+def test_capture_waits_for_a_list_still_in_flight():
+    """A list whose upload is queued behind other work of an eager call's stream: it is on the device
+    when the capture on another stream ends, since the graph's launches wait for nothing outside the graph."""
+    import torch
+    from paper_2607_01701_amd import attn_fwd, t2v_release_cache
+    pack = make_pack([300, 129], 2, 128, seed=97)
+    d = dev_inputs(pack)
+    want, want_lse = (x.clone() for x in attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale))
+    out, lse, out2, lse2 = (torch.empty_like(x) for x in (want, want_lse, want, want_lse))
+    x = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    y = x @ x
+    t2v_release_cache()
+    log("case capture with the list in flight")
+    busy, side, behind = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(busy):
+        for _ in range(100):
+            torch.mm(x, x, out=y)
+        behind.record()
+        attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, out=out2, lse=lse2)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        attn_fwd(d["q"], d["k"], d["v"], pack.cu_seqlens, pack.scale, out=out, lse=lse)
+        graph.capture_end()
+    assert behind.query(), "the captured call returned before the list was on the device"
+    for i in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(lse, want_lse), f"replay {i}"
+    assert torch.equal(out2, want) and torch.equal(lse2, want_lse)
+    t2v_release_cache()
