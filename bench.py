@@ -472,7 +472,7 @@ def write_summaries(bench_json, sweep_jsonl=None):
                      f"   {k[n]['hbm_bytes_per_launch'] / (k[n]['trace_avg_ms'] * 1e-3) / 1e12:5.2f} TB/s")
     lines += ["Algorithmic: fwd q,k,v,out + lse; bwd_pre out,dout + Delta, lse*log2e (and the lse read);",
               "bwd_dkdv q,k,v,dout,dk,dv + lse2, Delta; bwd_dq q,k,v,dout,dq + lse2, Delta.",
-              "The MFMA kernels re-read K/V (fwd, dQ) or Q/dO (dK/dV) once per 128-row tile, mostly from L2 and",
+              "The MFMA kernels re-read K/V (fwd, dQ) or Q/dO (dK/dV) once per 256-row tile, mostly from L2 and",
               "the MALL; their HBM rates sit far below the 8 TB/s peak, so they are not bandwidth bound.",
               "The Delta pass is HBM-bound; a workgroup owns one head and 64 consecutive tokens, so its [H, T]",
               "stores and lse reads are contiguous 256-byte runs."]

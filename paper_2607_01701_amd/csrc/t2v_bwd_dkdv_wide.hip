@@ -6,7 +6,7 @@
 // only wave per SIMD exposed (MFMAs busy 55% of cycles). Here every Q and dO operand feeds two
 // key blocks, so at D = 128 a step of 64 MFMAs takes 72 LDS reads (1.1 per MFMA instead of
 // 1.75) and half the LDS copies per MFMA, and the step is one hand-scheduled stream in which the
-// softmax arithmetic runs under the MFMAs (67% busy, at a clock that the card lowers from 1.96
+// softmax arithmetic runs under the MFMAs (64% busy, at a clock that the card lowers from 1.96
 // to 1.82 GHz as it reaches its power limit). Measured on the heterogeneous mix (24 x 128):
 // 34.9 -> 30.6 ms, 1,110 -> 1,267 TFLOP/s; results are bitwise those of the other kernel.
 //
